@@ -155,6 +155,7 @@ __global__ __launch_bounds__(TNT) void train_norm_bwd_kernel(const float* X, con
 }
 
 // ------------------------------------------------------------------ matrix products
+// Products with float32 weights (bf16 weights: train_gemm3.hip).
 // C[M][N] = R + (s . A)[M][K] op(B): BL = 0 reads B as [N][K] (x W^T with
 // W = [out][in]), BL = 1 as [K][N] (dY W).  64 x 64 output tiles over four
 // waves (32 x 32 each, 2 x 2 blocks of v_mfma_f32_16x16x4_f32, float32 in
@@ -168,14 +169,14 @@ __global__ __launch_bounds__(TNT) void train_norm_bwd_kernel(const float* X, con
 // bank conflicts on the transposed stores and the fragment reads)
 constexpr int GBM = 64, GBN = 64, GBK = 32, GLD = 68;
 
-template <int BL, class TB, bool ASC>
+template <int BL, bool ASC>
 __global__ __launch_bounds__(TNT) void train_gemm_kernel(TGemmArgs a) {
   __shared__ __attribute__((aligned(16))) float As[GBK][GLD];   // As[k][m]
   __shared__ __attribute__((aligned(16))) float Bs[GBK][GLD];   // Bs[k][n]
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wy = wave >> 1, wx = wave & 1;
   const int64_t m0 = (int64_t)blockIdx.y * GBM, n0 = (int64_t)blockIdx.x * GBN;
-  const TB* B = static_cast<const TB*>(a.B);
+  const float* B = a.B;
   const int64_t k_lo = (int64_t)blockIdx.z * a.kpiece;   // this piece's K range
   const int64_t k_hi = k_lo + a.kpiece < a.K ? k_lo + a.kpiece : a.K;
   const bool split = gridDim.z > 1;
@@ -910,7 +911,7 @@ hipError_t launch_train_norm_bwd(const float* X, const void* gain, const float* 
   return hipGetLastError();
 }
 
-hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, bool bf16, hipStream_t st) {
+hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, hipStream_t st) {
   if (a.M <= 0 || a.N <= 0) return hipSuccess;
   const int32_t ns = a.ksplit > 1 ? a.ksplit : 1;
   if (ns > 1 && (!a.part || a.kpiece % GBK || a.kpiece * (ns - 1) >= a.K || a.kpiece * ns < a.K))
@@ -919,16 +920,9 @@ hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, bool bf16, hipStrea
   if (ns == 1) g.kpiece = a.K;
   const dim3 grid((unsigned)((a.N + GBN - 1) / GBN), (unsigned)((a.M + GBM - 1) / GBM),
                   (unsigned)ns);
-  const bool asc = a.ascale != nullptr;
-#define SVL_TGEMM(BLV, TB, ASCV) train_gemm_kernel<BLV, TB, ASCV><<<grid, TNT, 0, st>>>(g)
-  if (bl == 0) {
-    if (bf16) { if (asc) SVL_TGEMM(0, uint16_t, true); else SVL_TGEMM(0, uint16_t, false); }
-    else { if (asc) SVL_TGEMM(0, float, true); else SVL_TGEMM(0, float, false); }
-  } else {
-    if (bf16) SVL_TGEMM(1, uint16_t, false);
-    else SVL_TGEMM(1, float, false);
-  }
-#undef SVL_TGEMM
+  if (bl == 1) train_gemm_kernel<1, false><<<grid, TNT, 0, st>>>(g);
+  else if (a.ascale) train_gemm_kernel<0, true><<<grid, TNT, 0, st>>>(g);
+  else train_gemm_kernel<0, false><<<grid, TNT, 0, st>>>(g);
   if (ns == 1) return hipGetLastError();
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <initializer_list>
 #include <string>
 
 #include "../../include/svl.h"
@@ -29,7 +30,24 @@ svl_status err(svl_status st, const char* fmt, ...) {
   return set_error(st, buf);
 }
 
-// K pieces of a product of M x N over K: a launch of fewer than 1024 64 x 64
+// Sizes of one launch of train_gemm3.hip: up to three (N, K), side by side in
+// the columns or along K.
+struct Prod {
+  bool ksegs;
+  int64_t N[3], K[3];
+  TGemm3Args shape(int64_t M) const {
+    TGemm3Args g{};
+    g.M = M;
+    g.ksegs = ksegs;
+    for (; g.nseg < 3 && N[g.nseg] > 0; ++g.nseg) {
+      g.seg[g.nseg].N = (int32_t)N[g.nseg];
+      g.seg[g.nseg].K = (int32_t)K[g.nseg];
+    }
+    return g;
+  }
+};
+
+// K pieces of a float32-weight product of M x N over K: a launch of fewer than 1024 64 x 64
 // tiles takes 2-4 pieces of at least 512 of K each, so that it holds about
 // 1280 workgroups, five per CU (640 tiles leave half the CUs one workgroup
 // short); ns = 1 keeps K whole.
@@ -102,11 +120,24 @@ TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, i
   t.dvec = take(M * A);
   t.pa = take(M * U);
   t.pf = take(M * U);
-  // every (N, K) the layer passes multiply
-  const int64_t shapes[][2] = {{A * d, D}, {KV * d, D}, {D, A * d}, {D, KV * d}, {F, D}, {D, F}};
-  for (const auto& nk : shapes) {
-    const KSplit ks = k_split(M, nk[0], nk[1]);
-    if (ks.ns > 1) t.kpart_floats = std::max(t.kpart_floats, ks.ns * M * nk[0]);
+  if (c.dtype == SVL_BF16) {
+    // every launch of the layer passes (train_gemm3.hip)
+    const int64_t Ad = A * d, Kd = KV * d;
+    const Prod prods[] = {{false, {Ad, Kd, Kd}, {D, D, D}}, {false, {D}, {Ad}}, {false, {F, F}, {D, D}},
+                          {false, {D}, {F}}, {false, {F}, {D}}, {true, {D, D}, {F, F}},
+                          {false, {Ad}, {D}}, {true, {D, D, D}, {Ad, Kd, Kd}}};
+    for (const Prod& p : prods) {
+      TGemm3Args g = p.shape(M);
+      train_gemm3_plan(g);
+      if (g.ksplit > 1) t.kpart_floats = std::max(t.kpart_floats, g.ksplit * M * (int64_t)g.ncols);
+    }
+  } else {
+    // every (N, K) the layer passes multiply
+    const int64_t shapes[][2] = {{A * d, D}, {KV * d, D}, {D, A * d}, {D, KV * d}, {F, D}, {D, F}};
+    for (const auto& nk : shapes) {
+      const KSplit ks = k_split(M, nk[0], nk[1]);
+      if (ks.ns > 1) t.kpart_floats = std::max(t.kpart_floats, ks.ns * M * nk[0]);
+    }
   }
   t.kpart = take(t.kpart_floats);
   t.total = off;
@@ -163,7 +194,7 @@ struct TrainRun {
     TGemmArgs g{};
     g.A = A;
     g.lda = lda;
-    g.B = Bw;
+    g.B = static_cast<const float*>(Bw);
     g.ldb = ldb;
     g.C = C;
     g.ldc = ldc;
@@ -184,7 +215,58 @@ struct TrainRun {
       g.kpiece = ks.kpiece;
       g.part = f(Lw.kpart);
     }
-    return launch_train_gemm(g, bl, bf16, st);
+    return launch_train_gemm(g, bl, st);
+  }
+
+  // One operand of a product: C (+)= A op(W), rows of A and C at their own strides.
+  struct Op {
+    const float* A;
+    int64_t lda;
+    const void* W;
+    int64_t ldw;
+    float* C;
+    int64_t N, K;
+  };
+
+  // The products of `ops` that share a launch: their own outputs from one A
+  // (ksegs = false), or one output, the sum of the products (ksegs = true);
+  // R is added to the (one) output.
+  hipError_t products(std::initializer_list<Op> ops, bool ksegs, int32_t bl, const float* R = nullptr,
+                      const float* ascale = nullptr, int32_t kg = 1) const {
+    hipError_t e = hipSuccess;
+    if (!bf16) {
+      const Op* first = ops.begin();
+      for (const Op& o : ops) {
+        const float* r = ksegs && &o != first ? o.C : R;
+        if ((e = gemm(o.A, o.lda, o.W, o.ldw, o.C, o.N, r, o.N, o.K, bl, ascale, kg)) != hipSuccess)
+          return e;
+      }
+      return e;
+    }
+    TGemm3Args g{};
+    g.M = M;
+    g.ksegs = ksegs;
+    for (const Op& o : ops) {
+      TSeg& t = g.seg[g.nseg++];
+      t.A = o.A;
+      t.lda = o.lda;
+      t.B = o.W;
+      t.ldb = o.ldw;
+      t.C = o.C;
+      t.ldc = o.N;
+      t.N = (int32_t)o.N;
+      t.K = (int32_t)o.K;
+    }
+    g.R = R;
+    g.ldr = g.seg[0].N;
+    g.ascale = ascale;
+    g.astride = (int64_t)c.n_layers * U;
+    g.S = (int32_t)S;
+    g.kg = kg;
+    train_gemm3_plan(g);
+    if (g.ksplit > 1 && g.ksplit * M * (int64_t)g.ncols > Lw.kpart_floats) return hipErrorInvalidValue;
+    g.part = f(Lw.kpart);
+    return launch_train_gemm3(g, bl, st);
   }
 
   TAttnArgs attn_args() const {
@@ -213,26 +295,26 @@ struct TrainRun {
     hipError_t e;
     if ((e = launch_train_norm(xs(l), w.attn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u),
                                f(Lw.r1), st)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.u), D, w.wq, D, f(Lw.q), A * d, nullptr, A * d, D, 0, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.u), D, w.wk, D, f(Lw.k), KV * d, nullptr, KV * d, D, 0, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.u), D, w.wv, D, f(Lw.v), KV * d, nullptr, KV * d, D, 0, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.u), D, w.wq, D, f(Lw.q), A * d, D},
+                       {f(Lw.u), D, w.wk, D, f(Lw.k), KV * d, D},
+                       {f(Lw.u), D, w.wv, D, f(Lw.v), KV * d, D}}, false, 0)) != hipSuccess) return e;
     if ((e = launch_train_rope(f(Lw.q), A * d, (int32_t)A, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
     if ((e = launch_train_rope(f(Lw.k), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
     TAttnArgs a = attn_args();
     a.out = f(Lw.o);
     if ((e = launch_train_attn(a, (int32_t)d, B, 0, st)) != hipSuccess) return e;
     // X1 = X_l + (M . O) Wo^T
-    if ((e = gemm(f(Lw.o), A * d, w.wo, A * d, f(Lw.x1), D, xs(l), D, A * d, 0, ms,
-                  (int32_t)(A / U * d))) != hipSuccess) return e;
+    if ((e = products({{f(Lw.o), A * d, w.wo, A * d, f(Lw.x1), D, A * d}}, false, 0, xs(l), ms,
+                      (int32_t)(A / U * d))) != hipSuccess) return e;
     if ((e = launch_train_norm(f(Lw.x1), w.ffn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u2),
                                f(Lw.r2), st)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.u2), D, w.w_gate, D, f(Lw.ag), F, nullptr, F, D, 0, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.u2), D, w.w_up, D, f(Lw.ae), F, nullptr, F, D, 0, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.u2), D, w.w_gate, D, f(Lw.ag), F, D},
+                       {f(Lw.u2), D, w.w_up, D, f(Lw.ae), F, D}}, false, 0)) != hipSuccess) return e;
     if ((e = launch_train_swiglu(f(Lw.ag), f(Lw.ae), M * F, f(Lw.hh), st)) != hipSuccess) return e;
     if (out) {
       // X_{l+1} = X1 + (M . H) Wd^T
-      if ((e = gemm(f(Lw.hh), F, w.w_down, F, out, D, f(Lw.x1), D, F, 0, ms, (int32_t)(F / U))) != hipSuccess)
-        return e;
+      if ((e = products({{f(Lw.hh), F, w.w_down, F, out, D, F}}, false, 0, f(Lw.x1), ms,
+                        (int32_t)(F / U))) != hipSuccess) return e;
     }
     return hipSuccess;
   }
@@ -247,17 +329,17 @@ struct TrainRun {
     const float2* tab = reinterpret_cast<const float2*>(ws + Lw.rope);
     hipError_t e;
     // FFN branch: dHm = dX2 Wd, then SwiGLU (gate / up gradients replace AG / AE)
-    if ((e = gemm(dX2, D, w.w_down, F, f(Lw.dh), F, nullptr, F, D, 1, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1)) != hipSuccess) return e;
     if ((e = launch_train_swiglu_bwd(f(Lw.dh), f(Lw.ag), f(Lw.ae), f(Lw.hh), ms, mstride,
                                      (int32_t)S, M, (int32_t)F, U, f(Lw.pf), st)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.ag), F, w.w_gate, D, f(Lw.du), D, nullptr, D, F, 1, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.ae), F, w.w_up, D, f(Lw.du), D, f(Lw.du), D, F, 1, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.ag), F, w.w_gate, D, f(Lw.du), D, F},
+                       {f(Lw.ae), F, w.w_up, D, f(Lw.du), D, F}}, true, 1)) != hipSuccess) return e;
     if ((e = launch_train_norm_bwd(f(Lw.x1), w.ffn_norm, f(Lw.r2), f(Lw.du), dX2, M, (int32_t)D,
                                    bf16, f(Lw.dx1), st)) != hipSuccess) return e;
     // attention branch: dOm = dX1 Wo, scaled in place by the masks into dO
     float* dO = f(Lw.dO);
     float* dQ = f(Lw.dq);
-    if ((e = gemm(f(Lw.dx1), D, w.wo, A * d, dO, A * d, nullptr, A * d, D, 1, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.dx1), D, w.wo, A * d, dO, A * d, D}}, false, 1)) != hipSuccess) return e;
     if ((e = launch_train_attn_mask_bwd(dO, f(Lw.o), ms, mstride, (int32_t)S, M, (int32_t)(A * d),
                                         U, f(Lw.pa), st)) != hipSuccess) return e;
     TAttnArgs a = attn_args();
@@ -269,9 +351,9 @@ struct TrainRun {
     if ((e = launch_train_attn(a, (int32_t)d, B, 2, st)) != hipSuccess) return e;
     if ((e = launch_train_rope(dQ, A * d, (int32_t)A, (int32_t)d, (int32_t)S, M, tab, -1.f, st)) != hipSuccess) return e;
     if ((e = launch_train_rope(f(Lw.dk), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, -1.f, st)) != hipSuccess) return e;
-    if ((e = gemm(dQ, A * d, w.wq, D, f(Lw.du), D, nullptr, D, A * d, 1, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.dk), KV * d, w.wk, D, f(Lw.du), D, f(Lw.du), D, KV * d, 1, nullptr, 1)) != hipSuccess) return e;
-    if ((e = gemm(f(Lw.dv), KV * d, w.wv, D, f(Lw.du), D, f(Lw.du), D, KV * d, 1, nullptr, 1)) != hipSuccess) return e;
+    if ((e = products({{dQ, A * d, w.wq, D, f(Lw.du), D, A * d},
+                       {f(Lw.dk), KV * d, w.wk, D, f(Lw.du), D, KV * d},
+                       {f(Lw.dv), KV * d, w.wv, D, f(Lw.du), D, KV * d}}, true, 1)) != hipSuccess) return e;
     if ((e = launch_train_norm_bwd(xs(l), w.attn_norm, f(Lw.r1), f(Lw.du), f(Lw.dx1), M,
                                    (int32_t)D, bf16, dX, st)) != hipSuccess) return e;
     return launch_train_mask_reduce(f(Lw.pa), f(Lw.pf), B, (int32_t)S, U, c.n_layers, l, f(Lw.dM), st);

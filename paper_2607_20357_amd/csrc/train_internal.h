@@ -24,11 +24,11 @@ struct TrainMaskArgs {
   float* steg;         // [B][(L-P) U] y (1 - y) / tau_comp
 };
 
-// C = R + (s . A) op(B) (see train_gemm_kernel).
+// C = R + (s . A) op(B), float32 weights (see train_gemm_kernel).
 struct TGemmArgs {
   const float* A;
   int64_t lda;
-  const void* B;       // weights, storage dtype
+  const float* B;      // weights
   int64_t ldb;
   float* C;
   int64_t ldc;
@@ -45,6 +45,40 @@ struct TGemmArgs {
   int64_t kpiece;
   float* part;
 };
+
+// Products with bf16 weights (train_gemm3.hip): up to three operands that share
+// a launch, either side by side in the columns (ksegs = false: C_s = A B_s, one
+// A) or along K (ksegs = true: one C = sum over s of A_s B_s).
+struct TSeg {
+  const float* A;
+  int64_t lda;
+  const void* B;        // bf16 weights
+  int64_t ldb;
+  float* C;
+  int64_t ldc;
+  int32_t N, K;         // N % 4 == 0, K % 16 == 0
+  int32_t ntn, chunks, col0;   // filled by train_gemm3_plan
+};
+struct TGemm3Args {
+  TSeg seg[3];
+  int32_t nseg;
+  bool ksegs;
+  int64_t M;
+  const float* R;       // nullptr, or added to C (one output; may equal it)
+  int64_t ldr;
+  const float* ascale;  // as in TGemmArgs (nseg == 1)
+  int64_t astride;
+  int32_t S, kg;
+  float* part;          // slices [ksplit][M][ncols] when ksplit > 1
+  // filled by train_gemm3_plan: tiles, output columns, K steps of 32 and pieces
+  int32_t mtiles, ntn, ncols, nchunks, ksplit, cpiece, ntiles;
+};
+struct KPieces {
+  int32_t ns;
+  int64_t chunks;
+};
+void train_gemm3_plan(TGemm3Args& a);
+hipError_t launch_train_gemm3(const TGemm3Args& a, int32_t bl, hipStream_t st);
 
 // Attention of one layer over B samples of S rows (buffers [B S][heads d]).
 struct TAttnArgs {
@@ -70,7 +104,7 @@ hipError_t launch_train_norm_bwd(const float* X, const void* gain, const float* 
                                  const float* dRes, int64_t M, int32_t D, bool bf16, float* dX,
                                  hipStream_t st);
 // bl: 0 reads B as [N][K], 1 as [K][N] (ascale only with bl == 0)
-hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, bool bf16, hipStream_t st);
+hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, hipStream_t st);
 hipError_t launch_train_rope(float* X, int64_t ld, int32_t nheads, int32_t d, int32_t S, int64_t M,
                              const float2* tab, float sgn, hipStream_t st);
 // which: 0 forward (O, lse), 1 query gradient (dQ, Dv), 2 key / value gradients

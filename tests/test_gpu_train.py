@@ -165,3 +165,20 @@ def test_train_headline_width():
     and 64 text tokens), two layers, the layer-head controller from layer 1."""
     w = W.scaled(W.get_workload("llava7b_b1_keep25"), n_layers=2, name="llava7b_train_width")
     _run(w, 8, 1, 4)
+
+
+@pytest.mark.parametrize("batch,n_vision,n_text", [(1, 1, 0), (1, 60, 4), (1, 100, 27), (2, 50, 14),
+                                                   (1, 120, 9), (3, 77, 9)])
+def test_train_bf16_product_tile_edges(batch, n_vision, n_text):
+    """bf16-weight products (128 x 256 output tiles, K in steps of 32, K pieces):
+    1, 64, 127, 128, 129 and 258 rows; 320 output columns (a full tile and a
+    ragged one), 64 columns (K / V heads) and 192 + 64 + 64 columns side by side,
+    reductions of 192 and 64 beside each other along K, and samples that cross
+    a tile's rows under their own unit masks.  Without noise: with it the first
+    token's 1 - y falls below float64's resolution in the oracle."""
+    base = _tiny(batch)
+    shape = dataclasses.replace(base.shape, d_model=320, n_heads=3, n_kv_heads=1, head_dim=64,
+                                d_ffn=768, n_groups=3, dtype="bf16")
+    w = dataclasses.replace(base, shape=shape, n_vision=n_vision, n_text=n_text,
+                            name=f"train_edges_b{batch}_{n_vision}_{n_text}")
+    _run(w, 12, 1, 3, noise=False)
