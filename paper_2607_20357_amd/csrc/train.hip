@@ -762,7 +762,7 @@ __global__ void train_swiglu_kernel(const float* AG, const float* AE, int64_t n,
 // Per row: part[m][u] = sum over unit u's channels of dHm . H; then, with the
 // unit's mask s, dH = s dHm and the gate / up gradients replace AG and AE.
 __global__ __launch_bounds__(TNT) void train_swiglu_bwd_kernel(const float* dHm, float* AG,
-                                                               float* AE, const float* H,
+                                                               float* AE,
                                                                const float* mrow, int64_t mstride,
                                                                int32_t S, int32_t F, int32_t U,
                                                                float* part) {
@@ -776,9 +776,10 @@ __global__ __launch_bounds__(TNT) void train_swiglu_bwd_kernel(const float* dHm,
     for (int c = u * w + threadIdx.x; c < (u + 1) * w; c += TNT) {
       const int64_t q = m * F + c;
       const float dh = dHm[q];
-      dot += dh * H[q];
       const float x = AG[q], e = AE[q];
-      const float sg = 1.0f / (1.0f + expf(-x));
+      const float ex = 1.0f + expf(-x);
+      dot += dh * (x / ex * e);   // H as the forward forms it
+      const float sg = 1.0f / ex;
       const float dm = dh * s;
       AG[q] = dm * e * sg * (1.0f + x * (1.0f - sg));
       AE[q] = dm * x * sg;
@@ -967,11 +968,11 @@ hipError_t launch_train_swiglu(const float* AG, const float* AE, int64_t n, floa
   return hipGetLastError();
 }
 
-hipError_t launch_train_swiglu_bwd(const float* dHm, float* AG, float* AE, const float* H,
-                                   const float* mrow, int64_t mstride, int32_t S, int64_t M,
+hipError_t launch_train_swiglu_bwd(const float* dHm, float* AG, float* AE, const float* mrow,
+                                   int64_t mstride, int32_t S, int64_t M,
                                    int32_t F, int32_t U, float* part, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  train_swiglu_bwd_kernel<<<(unsigned)M, TNT, 0, st>>>(dHm, AG, AE, H, mrow, mstride, S, F, U, part);
+  train_swiglu_bwd_kernel<<<(unsigned)M, TNT, 0, st>>>(dHm, AG, AE, mrow, mstride, S, F, U, part);
   return hipGetLastError();
 }
 

@@ -72,13 +72,24 @@ struct TrainLayout {
   int64_t xs;                          // X_0 .. X_{L-1}, [L][M][D]
   int64_t mtok, stet, mfull, steg, dM; // masks and straight-through factors
   int64_t rope;                        // (cos, sin)[S][d/2]
-  int64_t u, r1, q, k, v, o, lse, x1, u2, r2, ag, ae, hh;   // one layer's forward
+  int64_t u, u2, hh;                   // a layer's forward, not needed by its backward
+  // what the backward of a layer reads from its forward: one set per layer
+  // (layer l's at + l * lstride), or one set in all (lstride = 0), refilled from
+  // the layer's input before its backward
+  int64_t r1, q, k, v, o, lse, x1, r2, ag, ae;
+  int64_t lstride;
   int64_t dxa, dxb, dx1, du, dh, dO, dq, dk, dv, dvec, pa, pf;  // its backward
   int64_t kpart, kpart_floats;         // the K pieces' slices of one product
   int64_t total;
 };
 
-TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, int32_t T) {
+// The layers' sets are all kept when they take at most this much: it saves the
+// second forward of every layer but its down projection, 28% of the products of
+// a step (7B shape, 640 rows: 109 MB a layer, 3.5 GB in all).
+constexpr int64_t kKeepBytes = int64_t(16) << 30;
+
+TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, int32_t T,
+                         bool keep) {
   const int64_t S = (int64_t)N + T, M = (int64_t)B * S, D = c.d_model, F = c.d_ffn;
   const int64_t A = c.n_heads, KV = c.n_kv_heads, d = c.head_dim, L = c.n_layers;
   TrainLayout t{};
@@ -96,6 +107,9 @@ TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, i
   t.dM = take((int64_t)B * L * U);
   t.rope = take(S * (d / 2) * 2);
   t.u = take(M * D);
+  t.u2 = take(M * D);
+  t.hh = take(M * F);
+  const int64_t set0 = off;
   t.r1 = take(M);
   t.q = take(M * A * d);
   t.k = take(M * KV * d);
@@ -103,11 +117,13 @@ TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, i
   t.o = take(M * A * d);
   t.lse = take(M * A);
   t.x1 = take(M * D);
-  t.u2 = take(M * D);
   t.r2 = take(M);
   t.ag = take(M * F);
   t.ae = take(M * F);
-  t.hh = take(M * F);
+  if (keep && (off - set0) <= kKeepBytes / L) {
+    t.lstride = off - set0;
+    off += (L - 1) * t.lstride;
+  }
   t.dxa = take(M * D);
   t.dxb = take(M * D);
   t.dx1 = take(M * D);
@@ -186,6 +202,8 @@ struct TrainRun {
   hipStream_t st;
 
   float* f(int64_t off) const { return reinterpret_cast<float*>(ws + off); }
+  // layer l's copy of a region of its set
+  float* fl(int64_t off, int32_t l) const { return f(off + l * Lw.lstride); }
   float* xs(int32_t l) const { return f(Lw.xs) + (int64_t)l * M * c.d_model; }
 
   hipError_t gemm(const float* A, int64_t lda, const void* Bw, int64_t ldb, float* C, int64_t ldc,
@@ -269,14 +287,14 @@ struct TrainRun {
     return launch_train_gemm3(g, bl, st);
   }
 
-  TAttnArgs attn_args() const {
+  TAttnArgs attn_args(int32_t l) const {
     TAttnArgs a{};
-    a.Q = f(Lw.q);
-    a.K = f(Lw.k);
-    a.V = f(Lw.v);
-    a.O = f(Lw.o);
+    a.Q = fl(Lw.q, l);
+    a.K = fl(Lw.k, l);
+    a.V = fl(Lw.v, l);
+    a.O = fl(Lw.o, l);
     a.dO = nullptr;
-    a.lse = f(Lw.lse);
+    a.lse = fl(Lw.lse, l);
     a.Dv = f(Lw.dvec);
     a.S = S;
     a.A = c.n_heads;
@@ -285,7 +303,7 @@ struct TrainRun {
     return a;
   }
 
-  // Forward of layer l from X_l: fills the layer intermediates; with `out`,
+  // Forward of layer l from X_l: fills the layer's set; with `out`,
   // also the down projection into out (X_{l+1}).
   hipError_t layer_forward(int32_t l, float* out) const {
     const svl_layer_weights& w = W[l];
@@ -294,32 +312,32 @@ struct TrainRun {
     const float2* tab = reinterpret_cast<const float2*>(ws + Lw.rope);
     hipError_t e;
     if ((e = launch_train_norm(xs(l), w.attn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u),
-                               f(Lw.r1), st)) != hipSuccess) return e;
-    if ((e = products({{f(Lw.u), D, w.wq, D, f(Lw.q), A * d, D},
-                       {f(Lw.u), D, w.wk, D, f(Lw.k), KV * d, D},
-                       {f(Lw.u), D, w.wv, D, f(Lw.v), KV * d, D}}, false, 0)) != hipSuccess) return e;
-    if ((e = launch_train_rope(f(Lw.q), A * d, (int32_t)A, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
-    if ((e = launch_train_rope(f(Lw.k), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
-    TAttnArgs a = attn_args();
-    a.out = f(Lw.o);
+                               fl(Lw.r1, l), st)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.u), D, w.wq, D, fl(Lw.q, l), A * d, D},
+                       {f(Lw.u), D, w.wk, D, fl(Lw.k, l), KV * d, D},
+                       {f(Lw.u), D, w.wv, D, fl(Lw.v, l), KV * d, D}}, false, 0)) != hipSuccess) return e;
+    if ((e = launch_train_rope(fl(Lw.q, l), A * d, (int32_t)A, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
+    if ((e = launch_train_rope(fl(Lw.k, l), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
+    TAttnArgs a = attn_args(l);
+    a.out = fl(Lw.o, l);
     if ((e = launch_train_attn(a, (int32_t)d, B, 0, st)) != hipSuccess) return e;
     // X1 = X_l + (M . O) Wo^T
-    if ((e = products({{f(Lw.o), A * d, w.wo, A * d, f(Lw.x1), D, A * d}}, false, 0, xs(l), ms,
+    if ((e = products({{fl(Lw.o, l), A * d, w.wo, A * d, fl(Lw.x1, l), D, A * d}}, false, 0, xs(l), ms,
                       (int32_t)(A / U * d))) != hipSuccess) return e;
-    if ((e = launch_train_norm(f(Lw.x1), w.ffn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u2),
-                               f(Lw.r2), st)) != hipSuccess) return e;
-    if ((e = products({{f(Lw.u2), D, w.w_gate, D, f(Lw.ag), F, D},
-                       {f(Lw.u2), D, w.w_up, D, f(Lw.ae), F, D}}, false, 0)) != hipSuccess) return e;
-    if ((e = launch_train_swiglu(f(Lw.ag), f(Lw.ae), M * F, f(Lw.hh), st)) != hipSuccess) return e;
+    if ((e = launch_train_norm(fl(Lw.x1, l), w.ffn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u2),
+                               fl(Lw.r2, l), st)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.u2), D, w.w_gate, D, fl(Lw.ag, l), F, D},
+                       {f(Lw.u2), D, w.w_up, D, fl(Lw.ae, l), F, D}}, false, 0)) != hipSuccess) return e;
     if (out) {
+      if ((e = launch_train_swiglu(fl(Lw.ag, l), fl(Lw.ae, l), M * F, f(Lw.hh), st)) != hipSuccess) return e;
       // X_{l+1} = X1 + (M . H) Wd^T
-      if ((e = products({{f(Lw.hh), F, w.w_down, F, out, D, F}}, false, 0, f(Lw.x1), ms,
+      if ((e = products({{f(Lw.hh), F, w.w_down, F, out, D, F}}, false, 0, fl(Lw.x1, l), ms,
                         (int32_t)(F / U))) != hipSuccess) return e;
     }
     return hipSuccess;
   }
 
-  // Backward of layer l (its intermediates in the workspace): dX2 = dL/dX_{l+1}
+  // Backward of layer l (its set in the workspace): dX2 = dL/dX_{l+1}
   // in, dX = dL/dX_l out, and the layer's mask gradients into dM.
   hipError_t layer_backward(int32_t l, const float* dX2, float* dX) const {
     const svl_layer_weights& w = W[l];
@@ -330,19 +348,19 @@ struct TrainRun {
     hipError_t e;
     // FFN branch: dHm = dX2 Wd, then SwiGLU (gate / up gradients replace AG / AE)
     if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1)) != hipSuccess) return e;
-    if ((e = launch_train_swiglu_bwd(f(Lw.dh), f(Lw.ag), f(Lw.ae), f(Lw.hh), ms, mstride,
+    if ((e = launch_train_swiglu_bwd(f(Lw.dh), fl(Lw.ag, l), fl(Lw.ae, l), ms, mstride,
                                      (int32_t)S, M, (int32_t)F, U, f(Lw.pf), st)) != hipSuccess) return e;
-    if ((e = products({{f(Lw.ag), F, w.w_gate, D, f(Lw.du), D, F},
-                       {f(Lw.ae), F, w.w_up, D, f(Lw.du), D, F}}, true, 1)) != hipSuccess) return e;
-    if ((e = launch_train_norm_bwd(f(Lw.x1), w.ffn_norm, f(Lw.r2), f(Lw.du), dX2, M, (int32_t)D,
+    if ((e = products({{fl(Lw.ag, l), F, w.w_gate, D, f(Lw.du), D, F},
+                       {fl(Lw.ae, l), F, w.w_up, D, f(Lw.du), D, F}}, true, 1)) != hipSuccess) return e;
+    if ((e = launch_train_norm_bwd(fl(Lw.x1, l), w.ffn_norm, fl(Lw.r2, l), f(Lw.du), dX2, M, (int32_t)D,
                                    bf16, f(Lw.dx1), st)) != hipSuccess) return e;
     // attention branch: dOm = dX1 Wo, scaled in place by the masks into dO
     float* dO = f(Lw.dO);
     float* dQ = f(Lw.dq);
     if ((e = products({{f(Lw.dx1), D, w.wo, A * d, dO, A * d, D}}, false, 1)) != hipSuccess) return e;
-    if ((e = launch_train_attn_mask_bwd(dO, f(Lw.o), ms, mstride, (int32_t)S, M, (int32_t)(A * d),
+    if ((e = launch_train_attn_mask_bwd(dO, fl(Lw.o, l), ms, mstride, (int32_t)S, M, (int32_t)(A * d),
                                         U, f(Lw.pa), st)) != hipSuccess) return e;
-    TAttnArgs a = attn_args();
+    TAttnArgs a = attn_args(l);
     a.dO = dO;
     a.out = dQ;
     if ((e = launch_train_attn(a, (int32_t)d, B, 1, st)) != hipSuccess) return e;
@@ -354,7 +372,7 @@ struct TrainRun {
     if ((e = products({{dQ, A * d, w.wq, D, f(Lw.du), D, A * d},
                        {f(Lw.dk), KV * d, w.wk, D, f(Lw.du), D, KV * d},
                        {f(Lw.dv), KV * d, w.wv, D, f(Lw.du), D, KV * d}}, true, 1)) != hipSuccess) return e;
-    if ((e = launch_train_norm_bwd(xs(l), w.attn_norm, f(Lw.r1), f(Lw.du), f(Lw.dx1), M,
+    if ((e = launch_train_norm_bwd(xs(l), w.attn_norm, fl(Lw.r1, l), f(Lw.du), f(Lw.dx1), M,
                                    (int32_t)D, bf16, dX, st)) != hipSuccess) return e;
     return launch_train_mask_reduce(f(Lw.pa), f(Lw.pf), B, (int32_t)S, U, c.n_layers, l, f(Lw.dM), st);
   }
@@ -370,7 +388,7 @@ extern "C" {
 size_t svl_train_workspace_bytes(const svl_config* cfg, const svl_train_params* params,
                                  int32_t batch, int32_t n_vision, int32_t n_text) {
   if (check_train(cfg, params, batch, n_vision, n_text) != SVL_OK) return 0;
-  return (size_t)train_layout(*cfg, params->units, batch, n_vision, n_text).total;
+  return (size_t)train_layout(*cfg, params->units, batch, n_vision, n_text, true).total;
 }
 
 svl_status svl_train_step(const svl_config* cfg, const svl_layer_weights* layers,
@@ -408,7 +426,9 @@ svl_status svl_train_step(const svl_config* cfg, const svl_layer_weights* layers
   }
   if (!ws) return err(SVL_E_NULL, "workspace is NULL");
   if (!is_aligned16(ws)) return err(SVL_E_ALIGN, "workspace not 16-byte aligned");
-  const TrainLayout Lw = train_layout(c, U, B, N, T);
+  // a workspace without room for every layer's set runs each forward again
+  TrainLayout Lw = train_layout(c, U, B, N, T, true);
+  if ((int64_t)ws_bytes < Lw.total) Lw = train_layout(c, U, B, N, T, false);
   if ((int64_t)ws_bytes < Lw.total)
     return err(SVL_E_WORKSPACE, "workspace %zu bytes < %lld needed", ws_bytes, (long long)Lw.total);
 
@@ -451,7 +471,7 @@ svl_status svl_train_step(const svl_config* cfg, const svl_layer_weights* layers
   float* bufs[2] = {run.f(Lw.dxa), run.f(Lw.dxb)};
   for (int32_t l = c.n_layers - 1; l >= 0; --l) {
     float* dnext = bufs[l & 1];
-    if ((e = run.layer_forward(l, nullptr)) != hipSuccess) return hip_err(e, "recompute");
+    if (!Lw.lstride && (e = run.layer_forward(l, nullptr)) != hipSuccess) return hip_err(e, "recompute");
     if ((e = run.layer_backward(l, dcur, dnext)) != hipSuccess) return hip_err(e, "backward");
     dcur = dnext;
   }

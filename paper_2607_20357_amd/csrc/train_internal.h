@@ -112,8 +112,8 @@ hipError_t launch_train_attn(const TAttnArgs& a, int32_t head_dim, int32_t B, in
                              hipStream_t st);
 hipError_t launch_train_swiglu(const float* AG, const float* AE, int64_t n, float* H,
                                hipStream_t st);
-hipError_t launch_train_swiglu_bwd(const float* dHm, float* AG, float* AE, const float* H,
-                                   const float* mrow, int64_t mstride, int32_t S, int64_t M,
+hipError_t launch_train_swiglu_bwd(const float* dHm, float* AG, float* AE, const float* mrow,
+                                   int64_t mstride, int32_t S, int64_t M,
                                    int32_t F, int32_t U, float* part, hipStream_t st);
 hipError_t launch_train_attn_mask_bwd(float* dOm, const float* O, const float* mrow,
                                       int64_t mstride, int32_t S, int64_t M, int32_t W, int32_t U,

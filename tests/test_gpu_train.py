@@ -182,3 +182,25 @@ def test_train_bf16_product_tile_edges(batch, n_vision, n_text):
     w = dataclasses.replace(base, shape=shape, n_vision=n_vision, n_text=n_text,
                             name=f"train_edges_b{batch}_{n_vision}_{n_text}")
     _run(w, 12, 1, 3, noise=False)
+
+
+def test_train_without_room_for_every_layers_set():
+    """A workspace below svl_train_workspace_bytes that holds one layer's forward
+    set: each forward runs again before its backward, with the same results."""
+    w = W.scaled(W.get_workload("llava7b_b1_keep25"), n_layers=3, d_model=512, n_heads=4,
+                 n_kv_heads=4, d_ffn=1024, batch=2, n_vision=70, n_text=20, name="train_small_ws")
+    s = w.shape
+    B, N, T, D = 2, 70, 20, s.d_model
+    cfg = svl.make_config(s)
+    vision, text = W.draw_hidden(w, 13, device="cuda")
+    layers = svl.LayerTable([W.draw_layer_weights(w, l, 13, device="cuda") for l in range(3)])
+    rng = np.random.default_rng(13)
+    t = lambda *shape: torch.from_numpy(rng.standard_normal(shape).astype(np.float32)).cuda()
+    z, g, G = t(B, N), t(B, 8), t(B, N + T, D)
+    prm = svl.svl_train_params(0.5, 0.5, 1, 4)
+    ws = svl.alloc_train_workspace(cfg, prm, B, N, T)
+    a = svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws)
+    b = svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws[:ws.numel() - 256])
+    torch.cuda.synchronize()
+    for k in a:
+        assert torch.equal(a[k], b[k]), k
