@@ -148,8 +148,8 @@ constexpr int MFMA_BM = 256, MFMA_BK = 64;
 constexpr int MFMA_MAX_SPLIT = 8;
 constexpr int MFMA_MAX_NB = 8;
 constexpr int MFMA_PARTIAL_ROWS = 4096;   // split pieces x rows the partial buffer holds
-constexpr int F32_BM = 64, F32_BN = 64, F32_BK = 16;
-constexpr int F32_SWIGLU_CH = 32;
+constexpr int F32_BM = 32, F32_BN = 32;
+constexpr int F32_SWIGLU_CH = 16;
 constexpr int ATTN_BQ = 64;          // query rows per attention workgroup
 constexpr int ATTN_BQ_SHORT = 32;    // 16-bit path, launches too short to fill the chip
 

@@ -51,6 +51,24 @@ def test_prefill_tiny_f32_other_seeds():
         _check_prefill(W.get_workload("tiny_f32"), seed)
 
 
+@pytest.mark.parametrize("n_vision,n_text,head_dim,d_ffn", [
+    (1, 0, 64, 688), (20, 12, 32, 84), (40, 13, 64, 692), (90, 40, 128, 1000), (130, 31, 32, 62)])
+def test_prefill_f32_tile_edges(n_vision, n_text, head_dim, d_ffn):
+    """Float32 products (32 x 32 tiles, K chunks shared by four waves) and
+    attention (64-query tiles): 1, 22, 33, 85 and 96 rows; FFN slices of 172, 21,
+    173, 250 and 31 channels, so that K chunks and rows start off 16-byte
+    boundaries; fewer chunks than waves and more."""
+    import dataclasses
+    base = W.get_workload("tiny_f32")
+    groups = 4 if d_ffn % 4 == 0 else 2
+    shape = dataclasses.replace(base.shape, d_model=4 * head_dim, head_dim=head_dim, d_ffn=d_ffn,
+                                n_groups=groups)
+    w = dataclasses.replace(base, shape=shape, batch=2, n_vision=n_vision, n_text=n_text,
+                            name=f"f32_edges_{n_vision}_{n_text}_{head_dim}_{d_ffn}")
+    for e in _check_prefill(w, seed=5):
+        assert e <= 5e-6     # sums of at most 1000 products: 1000 x 2^-24 = 6e-5 at worst
+
+
 def test_prefill_llava7b_headline_full_size():
     """The benchmarked workload at its real shape: 32 layers, d 4096, keep 144."""
     _check_prefill(W.get_workload("llava7b_b1_keep25"))
