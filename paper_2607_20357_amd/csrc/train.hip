@@ -287,6 +287,107 @@ __global__ __launch_bounds__(TNT) void train_gemm_kernel(TGemmArgs a) {
   }
 }
 
+// The same product for the small decoders' launches (train_small_product),
+// which latency bounds: 32 x 32 tiles, the
+// four waves of a workgroup taking 64 columns of K in turn, fragments loaded
+// straight into registers and the next 64 columns in flight meanwhile, and the
+// four sums added in wave order through LDS at the end.  Lane (r, q) holds
+// 4 consecutive k of its row at k = 16 s + 4 q, in the same order for A and B.
+// 160 rows x 256-688 columns x 256-688: 9-36 us per product with 64 x 64 tiles
+// (12-33 workgroups), 6-9 us here.
+template <int BL, bool ASC>
+__global__ __launch_bounds__(TNT) void train_gemm_small_kernel(TGemmArgs a) {
+  __shared__ float red[4][16][64];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int fr = lane & 15, fq = lane >> 4;
+  const int64_t m0 = (int64_t)blockIdx.y * 32, n0 = (int64_t)blockIdx.x * 32;
+  const float* pa[2];
+  const float* pb[2];
+  const float* srow[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int64_t m = m0 + 16 * i + fr, n = n0 + 16 * i + fr;
+    pa[i] = m < a.M ? a.A + m * a.lda : nullptr;
+    pb[i] = n < a.N ? a.B + (BL == 0 ? n * a.ldb : n) : nullptr;
+    if constexpr (ASC) srow[i] = a.ascale + (m < a.M ? (m / a.S) * a.astride : 0);
+  }
+  const int64_t ks = (a.K + 63) / 64;   // steps of 64 (K % 16 == 0: the last may be shorter)
+  float4 v[2][4][4];                    // [step parity][16 columns][A rows, B columns]
+  auto load = [&](int64_t c, float4 (&x)[4][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int64_t k = c * 64 + 16 * s + 4 * fq;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        x[s][i] = x[s][2 + i] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (k >= a.K) continue;
+        if (pa[i]) {
+          x[s][i] = *reinterpret_cast<const float4*>(pa[i] + k);
+          if constexpr (ASC) x[s][i] = f4scale(x[s][i], srow[i][(uint32_t)k / (uint32_t)a.kg]);
+        }
+        if (pb[i]) {
+          if constexpr (BL == 0) {
+            x[s][2 + i] = *reinterpret_cast<const float4*>(pb[i] + k);
+          } else {
+            const float* p = pb[i] + k * a.ldb;
+            x[s][2 + i] = make_float4(p[0], p[a.ldb], p[2 * a.ldb], p[3 * a.ldb]);
+          }
+        }
+      }
+    }
+  };
+  floatx4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+  auto mul = [&](const float4 (&x)[4][4]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        auto at = [&](int o) {
+          return e == 0 ? x[s][o].x : e == 1 ? x[s][o].y : e == 2 ? x[s][o].z : x[s][o].w;
+        };
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(at(i), at(2 + j), acc[i][j], 0, 0, 0);
+      }
+  };
+  int64_t c = wave;
+  if (c < ks) load(c, v[0]);
+  while (c < ks) {
+    if (c + 4 < ks) load(c + 4, v[1]);
+    mul(v[0]);
+    c += 4;
+    if (c >= ks) break;
+    if (c + 4 < ks) load(c + 4, v[0]);
+    mul(v[1]);
+    c += 4;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[wave][8 * i + 4 * j + r][lane] = acc[i][j][r];
+  __syncthreads();
+  // wave w finishes block (w / 2, w % 2)
+  const int64_t col = n0 + 16 * (wave & 1) + fr;
+  if (col >= a.N) return;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t row = m0 + 16 * (wave >> 1) + 4 * fq + r;
+    if (row >= a.M) continue;
+    const int q = 4 * wave + r;
+    float o = ((red[0][q][lane] + red[1][q][lane]) + red[2][q][lane]) + red[3][q][lane];
+    if (a.R) o = a.R[row * a.ldr + col] + o;
+    a.C[row * a.ldc + col] = o;
+  }
+}
+
 // C = R + the K pieces' slices added in piece order, four columns per thread.
 __global__ void train_splitk_reduce_kernel(const float* part, int32_t ns, int64_t M, int64_t N,
                                            const float* R, int64_t ldr, float* C, int64_t ldc) {
@@ -917,6 +1018,13 @@ hipError_t launch_train_gemm(const TGemmArgs& a, int32_t bl, hipStream_t st) {
   const int32_t ns = a.ksplit > 1 ? a.ksplit : 1;
   if (ns > 1 && (!a.part || a.kpiece % GBK || a.kpiece * (ns - 1) >= a.K || a.kpiece * ns < a.K))
     return hipErrorInvalidValue;
+  if (ns == 1 && train_small_product(a.M, a.N, a.K)) {
+    const dim3 grid((unsigned)((a.N + 31) / 32), (unsigned)((a.M + 31) / 32));
+    if (bl == 1) train_gemm_small_kernel<1, false><<<grid, TNT, 0, st>>>(a);
+    else if (a.ascale) train_gemm_small_kernel<0, true><<<grid, TNT, 0, st>>>(a);
+    else train_gemm_small_kernel<0, false><<<grid, TNT, 0, st>>>(a);
+    return hipGetLastError();
+  }
   TGemmArgs g = a;
   if (ns == 1) g.kpiece = a.K;
   const dim3 grid((unsigned)((a.N + GBN - 1) / GBN), (unsigned)((a.M + GBM - 1) / GBM),

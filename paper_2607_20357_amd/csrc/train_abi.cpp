@@ -59,6 +59,7 @@ struct KSplit {
 KSplit k_split(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int64_t ns = 1;
+  if (train_small_product(M, N, K)) return {1, K};
   if (tiles < 1024) ns = std::min<int64_t>({4, K / 512, (1280 + tiles - 1) / tiles});
   if (ns < 2) return {1, K};
   const int64_t kp = ((K + ns - 1) / ns + 31) / 32 * 32;

@@ -46,6 +46,16 @@ struct TGemmArgs {
   float* part;
 };
 
+// Float32-weight products that take 32 x 32 tiles whose waves share K
+// (train_gemm_small_kernel): too few 64 x 64 tiles for the CUs and too short a K
+// for K pieces.  Step times with and without, both sides of the line: 256 wide
+// 640 rows (40-110 tiles) 730 / 923 us, 1024 wide 160 rows (48-129 tiles)
+// 908 / 1018, 640 rows (160 tiles) 2315 / 1980; K of 2048 and more, 2048 wide
+// 160 rows (96 tiles) 2069 / 1644, 40 rows 1205 / 1062.
+inline bool train_small_product(int64_t M, int64_t N, int64_t K) {
+  return ((N + 63) / 64) * ((M + 63) / 64) < 160 && K <= 1024;
+}
+
 // Products with bf16 weights (train_gemm3.hip): up to three operands that share
 // a launch, either side by side in the columns (ksegs = false: C_s = A B_s, one
 // A) or along K (ksegs = true: one C = sum over s of A_s B_s).

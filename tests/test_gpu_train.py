@@ -204,3 +204,16 @@ def test_train_without_room_for_every_layers_set():
     torch.cuda.synchronize()
     for k in a:
         assert torch.equal(a[k], b[k]), k
+
+
+@pytest.mark.parametrize("batch,n_vision,n_text,d_model,d_ffn", [
+    (1, 1, 0, 256, 688), (1, 20, 13, 144, 272), (2, 40, 25, 528, 1040), (1, 600, 41, 1024, 1088)])
+def test_train_f32_product_tiles(batch, n_vision, n_text, d_model, d_ffn):
+    """Float32-weight products on both sides of the 32 x 32 / 64 x 64 tile rule: 1,
+    33, 130 and 641 rows; widths and reductions that end a 64-column step after
+    16 and 32 columns; a reduction just above the rule's 1024."""
+    base = _tiny(batch)
+    shape = dataclasses.replace(base.shape, d_model=d_model, d_ffn=d_ffn)
+    w = dataclasses.replace(base, shape=shape, n_vision=n_vision, n_text=n_text,
+                            name=f"train_f32_b{batch}_{n_vision}_{n_text}_{d_model}")
+    _run(w, 14, 1, 4, noise=False)
