@@ -176,11 +176,13 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
     }
   };
 
-  floatx4 acc[4][4];
+  // acc sums 512 columns of K at a time, total the whole piece: a sum of n terms
+  // in two levels rounds at the size of the short sums
+  floatx4 acc[4][4], total[4][4];
 #pragma unroll
   for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < 4; ++j) acc[i][j] = total[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
   const bool live = 64 * wm < rows && n0 + 64 * wn < N;   // the wave owns outputs
   auto compute = [&](int buf) __attribute__((always_inline)) {
     const uint16_t* S = sm + buf * G3_STAGE;
@@ -218,11 +220,20 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
       if (wave < 4) refill();
       if (live) compute(buf);
       if (wave >= 4) refill();
+      if (((c - c_lo) & 15) == 15 || c + 1 == c_hi) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            total[i][j] += acc[i][j];
+            acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+          }
+      }
       __syncthreads();
     }
   }
 
-  // acc[i][j][r] = C[64 wm + 16 i + 4 (lane / 16) + r][64 wn + 16 j + lane % 16]
+  // total[i][j][r] = C[64 wm + 16 i + 4 (lane / 16) + r][64 wn + 16 j + lane % 16]
   const bool split = a.ksplit > 1;
   float* C = split ? a.part + (int64_t)piece * a.M * a.ncols + (a.ksegs ? 0 : a.seg[sn].col0)
                    : a.seg[sn].C;
@@ -238,7 +249,7 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
       for (int r = 0; r < 4; ++r) {
         const int row = 64 * wm + 16 * i + 4 * (lane >> 4) + r;
         if (row >= rows) continue;
-        float o = acc[i][j][r];
+        float o = total[i][j][r];
         if (R) o += R[(m0 + row) * a.ldr + col];
         C[(m0 + row) * ldc + col] = o;
       }
