@@ -19,7 +19,7 @@ CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsvl.so")
 BUILD_DIR = os.path.join(ROOT, "_build")
 
-SOURCES = ["abi.cpp", "plan.cpp", "select_gather.hip", "norm_misc.hip", "gemm_mfma.hip",
+SOURCES = ["abi.cpp", "plan.cpp", "select_gather.hip", "norm_misc.hip", "gemm_mfma.hip", "gemm_lo.hip",
            "attn_mfma.hip", "fp32_path.hip", "finish.hip", "budget.cpp", "attn_decode.hip",
            "controller.hip", "budget_loss.hip", "gemv_decode.hip", "train_abi.cpp",
            "train.hip", "train_gemm3.hip"]

@@ -219,6 +219,22 @@ def test_layer_row_block_counts(compute):
         assert max(errs) <= tol_for(shape), errs
 
 
+@pytest.mark.parametrize("blocks", [2, 3, 4, 5, 6, 8])
+def test_layer_lo_parts_tile_widths(blocks):
+    """Gate/up tiles of every block count of the two-term bf16 products (d_ffn
+    fills 256 tiles of that width), K of 13 chunks (three weight stages and
+    one chunk), tiles of 250 rows (4 row blocks per multiplying wave) and of
+    17 (two waves with one block, two with none)."""
+    shape = W.ModelShape(n_layers=1, d_model=832, n_heads=13, n_kv_heads=13, head_dim=64,
+                         d_ffn=2048 * blocks, n_groups=1, dtype="bf16")
+    for rows in (250, 17):
+        print(f"two-term tiles of {blocks} blocks, {rows} rows", flush=True)
+        errs = _layer_case(shape, np.array([rows], np.int32), np.ones(1, np.uint8),
+                           np.ones((1, 13), np.uint8), np.ones((1, 1), np.uint8), compute="bf16")
+        print(f"  rel err per sample: {[f'{e:.2e}' for e in errs]}", flush=True)
+        assert max(errs) <= tol_for(shape), errs
+
+
 @pytest.mark.parametrize("split,compute", [(2, "f16"), (3, "f16"), (2, "bf16")])
 def test_layer_forced_paired_split(split, compute, monkeypatch):
     """The split-K QKV and gate/up path (float32 slices, then the finish
