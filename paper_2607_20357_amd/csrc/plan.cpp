@@ -243,13 +243,16 @@ struct MmBuild {
       --best_b;
     return finish(w, best_b, kernel_nb(best_b), 1);
   }
-  // Output and down projections: 4-block tiles; a skinny launch splits K
-  // into float32 partial slices (at least 2 chunks per piece, the slices
-  // within the partial buffer).
+  // Output and down projections: 4-block tiles; a launch whose tiles would
+  // leave half of the CUs idle or more splits K into float32 partial slices
+  // (at least 2 chunks per piece, the slices within the partial buffer).  The
+  // line is the number of tiles, not the rows of a sample: 350 rows (two M
+  // tiles, 128 tiles of a 4096-wide output) in one piece take 79 us (down) and
+  // 33 us (output), see the launch figures in gemm_mfma.hip.
   GemmLaunch finish_plain(ImageWriter& w, int32_t R, int32_t D, int64_t cap_floats,
                           bool rowvec = false) {
     int32_t s = 1;
-    if (!rowvec && !groups.empty() && max_rows <= kSkinnyRows) {
+    if (!rowvec && !groups.empty()) {
       int64_t base = 0;
       for (const auto& g : groups) base += (int64_t)cdiv(g.nrows, MFMA_BM) * cdiv(g.nblocks, 4);
       s = (int32_t)std::max<int64_t>(1, kTargetTiles / std::max<int64_t>(1, base));
