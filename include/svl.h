@@ -401,7 +401,8 @@ svl_status svl_workspace_status(const void *ws, size_t ws_bytes, uint32_t *statu
  *
  * Arithmetic: float32 throughout (weights and embeddings widened exactly
  * from the storage dtype; svl_config.compute is ignored); the forward of each
- * layer is recomputed from its stored input during the backward.
+ * layer is recomputed from its stored input during the backward unless the
+ * workspace holds every layer's intermediates.
  * Requirements beyond the config's: head_dim in {32, 64, 128}; d_model and
  * d_ffn multiples of 16; n_heads and d_ffn divisible by units, d_ffn / units
  * a multiple of 4 (SVL_E_SHAPE otherwise). */
@@ -418,6 +419,12 @@ typedef struct {
 size_t svl_train_workspace_bytes(const svl_config *cfg, const svl_train_params *params,
                                  int32_t batch, int32_t n_vision, int32_t n_text);
 
+/* Workspace bytes with which svl_train_step keeps every layer's forward
+ * intermediates for its backward instead of running each forward again (the
+ * above where they would take more than 16 GiB; 0 on bad arguments). */
+size_t svl_train_workspace_bytes_full(const svl_config *cfg, const svl_train_params *params,
+                                      int32_t batch, int32_t n_vision, int32_t n_text);
+
 /* One training step of the masked decoder (all pointers dev, row-major):
  *   logits       float [B][N] token logits z;  token_noise float [B][N] or NULL
  *   gate_logits  float [B][(L-P) U] (layer-major);  gate_noise same or NULL
@@ -427,7 +434,8 @@ size_t svl_train_workspace_bytes(const svl_config *cfg, const svl_train_params *
  *   token_mask   uint8 [B][N] (out);  unit_mask uint8 [B][(L-P) U] (out)
  *   grad_logits  float [B][N] (out, when grad_hidden is given)
  *   grad_gate    float [B][(L-P) U] (out, when grad_hidden is given)
- *   ws/ws_bytes: at least svl_train_workspace_bytes(...).
+ *   ws/ws_bytes: at least svl_train_workspace_bytes(...); with
+ *       svl_train_workspace_bytes_full(...) a step runs faster, same results.
  * Arrays with no elements (N = 0, or (L-P) U = 0) may be NULL.  Enqueued on
  * `stream`; nothing is synchronised. */
 svl_status svl_train_step(const svl_config *cfg, const svl_layer_weights *layers,

@@ -127,6 +127,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
                                     P, P, P, P, P, P, P, P, P, P, P]
     lib.svl_train_workspace_bytes.argtypes = [cfgp, ctypes.POINTER(svl_train_params), i32, i32, i32]
     lib.svl_train_workspace_bytes.restype = sz
+    lib.svl_train_workspace_bytes_full.argtypes = lib.svl_train_workspace_bytes.argtypes
+    lib.svl_train_workspace_bytes_full.restype = sz
     lib.svl_train_step.argtypes = [cfgp, ctypes.POINTER(svl_layer_weights),
                                    ctypes.POINTER(svl_train_params), i32, i32, i32, P, P, P, P, P,
                                    P, P, P, P, P, P, P, P, sz, P]
@@ -699,8 +701,15 @@ def svl_train_workspace_bytes(cfg: svl_config, params: svl_train_params, batch: 
 
 def alloc_train_workspace(cfg: svl_config, params: svl_train_params, batch: int, n_vision: int,
                           n_text: int, device="cuda") -> torch.Tensor:
+    """Room for every layer's forward intermediates (a step then runs no forward
+    twice), or the required bytes where the device has no memory for that."""
     n = svl_train_workspace_bytes(cfg, params, batch, n_vision, n_text)
-    return torch.empty(n, dtype=torch.uint8, device=device)
+    full = load_library().svl_train_workspace_bytes_full(ctypes.byref(cfg), ctypes.byref(params),
+                                                         int(batch), int(n_vision), int(n_text))
+    try:
+        return torch.empty(max(n, int(full)), dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return torch.empty(n, dtype=torch.uint8, device=device)
 
 
 def svl_train_step(cfg: svl_config, layers, params: svl_train_params, logits: torch.Tensor,

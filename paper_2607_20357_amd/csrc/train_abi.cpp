@@ -389,6 +389,12 @@ extern "C" {
 size_t svl_train_workspace_bytes(const svl_config* cfg, const svl_train_params* params,
                                  int32_t batch, int32_t n_vision, int32_t n_text) {
   if (check_train(cfg, params, batch, n_vision, n_text) != SVL_OK) return 0;
+  return (size_t)train_layout(*cfg, params->units, batch, n_vision, n_text, false).total;
+}
+
+size_t svl_train_workspace_bytes_full(const svl_config* cfg, const svl_train_params* params,
+                                      int32_t batch, int32_t n_vision, int32_t n_text) {
+  if (check_train(cfg, params, batch, n_vision, n_text) != SVL_OK) return 0;
   return (size_t)train_layout(*cfg, params->units, batch, n_vision, n_text, true).total;
 }
 

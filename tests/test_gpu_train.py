@@ -185,8 +185,8 @@ def test_train_bf16_product_tile_edges(batch, n_vision, n_text):
 
 
 def test_train_without_room_for_every_layers_set():
-    """A workspace below svl_train_workspace_bytes that holds one layer's forward
-    set: each forward runs again before its backward, with the same results."""
+    """A workspace of svl_train_workspace_bytes holds one layer's forward set:
+    each forward runs again before its backward, with the same results."""
     w = W.scaled(W.get_workload("llava7b_b1_keep25"), n_layers=3, d_model=512, n_heads=4,
                  n_kv_heads=4, d_ffn=1024, batch=2, n_vision=70, n_text=20, name="train_small_ws")
     s = w.shape
@@ -200,7 +200,9 @@ def test_train_without_room_for_every_layers_set():
     prm = svl.svl_train_params(0.5, 0.5, 1, 4)
     ws = svl.alloc_train_workspace(cfg, prm, B, N, T)
     a = svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws)
-    b = svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws[:ws.numel() - 256])
+    small = svl.svl_train_workspace_bytes(cfg, prm, B, N, T)
+    assert small < ws.numel()
+    b = svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws[:small])
     torch.cuda.synchronize()
     for k in a:
         assert torch.equal(a[k], b[k]), k
