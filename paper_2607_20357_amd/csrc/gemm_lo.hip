@@ -22,8 +22,10 @@
 //
 // Against eight waves that each load and multiply (same box, both in turn; a
 // LLaVA-7B prefill of 350 rows, 3 of 4 groups on): eight layers 2.65 -> 2.23
-// ms.  The single-term products (fp16) have half the MFMAs
-// per byte loaded and measured 5% slower in this form, so they keep theirs.
+// ms; one layer of six samples of 54-90 rows, whose tiles leave each wave one
+// row block, 570 -> 583 us.  The single-term products (fp16) have half the
+// MFMAs per byte loaded and measured 5% slower in this form, so they keep
+// theirs.
 #include <type_traits>
 #include <utility>
 

@@ -83,8 +83,7 @@ struct LayerMasks {
 };
 
 // Rows of a sample up to which the 16-bit MFMA GEMMs count a sample as
-// skinny (one M tile): the output and down projections then split K so the
-// launch still covers the CUs.
+// skinny (one M tile): a forced split of QKV and gate/up applies to those.
 constexpr int32_t kSkinnyRows = MFMA_BM;
 // Workgroups a launch aims for (one per CU).
 constexpr int32_t kTargetTiles = 256;
