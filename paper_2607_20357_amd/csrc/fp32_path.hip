@@ -279,7 +279,8 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a) {
     for (int n = 0; n < NBO; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[n][r] *= corr[r];
-    // O += P V (a wave reads only the P^T columns it wrote; LDS keeps a wave's order)
+    wave_lds_handoff();   // a wave reads only the P^T columns that its own lanes wrote
+    // O += P V
 #pragma unroll 4
     for (int k = 0; k < BKV; k += 4) {
       const float pa = u.pt[k + lg][qw + lr];

@@ -574,7 +574,8 @@ __global__ __launch_bounds__(TNT) void train_attn_fwd_kernel(TAttnArgs a) {
     for (int n = 0; n < NBO; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) o[n][r] *= corr[r];
-    // O += P V (the P^T writes above are the wave's own; LDS keeps a wave's order)
+    wave_lds_handoff();   // a wave reads only the P^T columns that its own lanes wrote
+    // O += P V
 #pragma unroll 4
     for (int k = 0; k < 64; k += 4) {
       const float pa = sm.u.pt[k + lg][qw + lr];
@@ -714,7 +715,8 @@ __global__ __launch_bounds__(TNT, 2) void train_attn_dq_kernel(TAttnArgs a) {   
       }
       *reinterpret_cast<float4*>(&sm.u.ds[16 * jb + lr][qw + 4 * lg]) = w;
     }
-    // dQ[q][d] += sum_k dS[q][k] K[k][d] (the ds writes above are the wave's own)
+    wave_lds_handoff();   // the columns of ds that the wave's own lanes wrote
+    // dQ[q][d] += sum_k dS[q][k] K[k][d]
 #pragma unroll 4
     for (int k = 0; k < 64; k += 4) {
       const float pa = sm.u.ds[k + lg][qw + lr];
@@ -809,6 +811,7 @@ __global__ __launch_bounds__(TNT) void train_attn_dkv_kernel(TAttnArgs a) {
         }
         *reinterpret_cast<float4*>(&sm.w[qj][kw + 4 * lg]) = pw[jb];
       }
+      wave_lds_handoff();   // the columns of w that the wave's own lanes wrote
       // dV[k][c] += sum_q P^T[k][q] dO[q][c]
 #pragma unroll 4
       for (int qq = 0; qq < 64; qq += 4) {
@@ -817,7 +820,8 @@ __global__ __launch_bounds__(TNT) void train_attn_dkv_kernel(TAttnArgs a) {
         for (int n = 0; n < NBO; ++n)
           gv[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(pa, sm.dot[16 * n + lr][qq + lg], gv[n], 0, 0, 0);
       }
-      // dS^T = P^T (dP^T - D) over the same columns (after this wave's reads above)
+      wave_lds_handoff();   // the wave's reads of P come before its stores of dS
+      // dS^T = P^T (dP^T - D) over the same columns
 #pragma unroll
       for (int jb = 0; jb < 4; ++jb) {
         const int qj = 16 * jb + lr;
@@ -829,6 +833,7 @@ __global__ __launch_bounds__(TNT) void train_attn_dkv_kernel(TAttnArgs a) {
         for (int r = 0; r < 4; ++r) wv[r] = pv[r] * (dpt[jb][r] - dq);
         *reinterpret_cast<float4*>(&sm.w[qj][kw + 4 * lg]) = w;
       }
+      wave_lds_handoff();   // and those before the reads of dS
       // dK[k][c] += sum_q dS^T[k][q] (Q scale)[q][c]
 #pragma unroll 4
       for (int qq = 0; qq < 64; qq += 4) {
