@@ -30,23 +30,6 @@ svl_status err(svl_status st, const char* fmt, ...) {
   return set_error(st, buf);
 }
 
-// Sizes of one launch of train_gemm3.hip: up to three (N, K), side by side in
-// the columns or along K.
-struct Prod {
-  bool ksegs;
-  int64_t N[3], K[3];
-  TGemm3Args shape(int64_t M) const {
-    TGemm3Args g{};
-    g.M = M;
-    g.ksegs = ksegs;
-    for (; g.nseg < 3 && N[g.nseg] > 0; ++g.nseg) {
-      g.seg[g.nseg].N = (int32_t)N[g.nseg];
-      g.seg[g.nseg].K = (int32_t)K[g.nseg];
-    }
-    return g;
-  }
-};
-
 // K pieces of a float32-weight product of M x N over K: a launch of fewer than 1024 64 x 64
 // tiles takes 2-4 pieces of at least 512 of K each, so that it holds about
 // 1280 workgroups, five per CU (640 tiles leave half the CUs one workgroup
@@ -59,7 +42,6 @@ struct KSplit {
 KSplit k_split(int64_t M, int64_t N, int64_t K) {
   const int64_t tiles = ((N + 63) / 64) * ((M + 63) / 64);
   int64_t ns = 1;
-  if (train_small_product(M, N, K)) return {1, K};
   if (tiles < 1024) ns = std::min<int64_t>({4, K / 512, (1280 + tiles - 1) / tiles});
   if (ns < 2) return {1, K};
   const int64_t kp = ((K + ns - 1) / ns + 31) / 32 * 32;
@@ -73,15 +55,27 @@ struct TrainLayout {
   int64_t xs;                          // X_0 .. X_{L-1}, [L][M][D]
   int64_t mtok, stet, mfull, steg, dM; // masks and straight-through factors
   int64_t rope;                        // (cos, sin)[S][d/2]
-  int64_t u, u2, hh;                   // a layer's forward, not needed by its backward
   // what the backward of a layer reads from its forward: one set per layer
   // (layer l's at + l * lstride), or one set in all (lstride = 0), refilled from
   // the layer's input before its backward
   int64_t r1, q, k, v, o, lse, x1, r2, ag, ae;
   int64_t lstride;
-  int64_t dxa, dxb, dx1, du, dh, dO, dq, dk, dv, dvec, pa, pf;  // its backward
-  int64_t kpart, kpart_floats;         // the K pieces' slices of one product
+  int64_t dxa, dxb, pa, pf;            // its backward: gradients in and out, partial sums of dM
+  // Regions side by side, in this order, so that the K pieces' slices of a
+  // product with bf16 weights can take, beside kpart, the neighbours that are
+  // dead at its launch (Slices below): the rest of the backward; the slices of
+  // a product; and a layer's forward that its backward does not need.
+  int64_t du, dx1, dh, dO, dq, dk, dv, dvec, kpart, hh, u, u2, end;
+  int64_t kpart_floats;
   int64_t total;
+};
+
+// [at, end) of the workspace: room for the slices of one launch's K pieces.  It
+// is the same in a workspace with every layer's set and in one without, so
+// both form the same sums.
+struct Slices {
+  int64_t at, end;
+  int64_t floats() const { return (end - at) / 4; }
 };
 
 // The layers' sets are all kept when they take at most this much: it saves the
@@ -107,9 +101,6 @@ TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, i
   t.steg = take((int64_t)B * L * U);
   t.dM = take((int64_t)B * L * U);
   t.rope = take(S * (d / 2) * 2);
-  t.u = take(M * D);
-  t.u2 = take(M * D);
-  t.hh = take(M * F);
   const int64_t set0 = off;
   t.r1 = take(M);
   t.q = take(M * A * d);
@@ -127,36 +118,27 @@ TrainLayout train_layout(const svl_config& c, int32_t U, int32_t B, int32_t N, i
   }
   t.dxa = take(M * D);
   t.dxb = take(M * D);
-  t.dx1 = take(M * D);
+  t.pa = take(M * U);
+  t.pf = take(M * U);
   t.du = take(M * D);
+  t.dx1 = take(M * D);
   t.dh = take(M * F);
   t.dO = take(M * A * d);
   t.dq = take(M * A * d);
   t.dk = take(M * KV * d);
   t.dv = take(M * KV * d);
   t.dvec = take(M * A);
-  t.pa = take(M * U);
-  t.pf = take(M * U);
-  if (c.dtype == SVL_BF16) {
-    // every launch of the layer passes (train_gemm3.hip)
-    const int64_t Ad = A * d, Kd = KV * d;
-    const Prod prods[] = {{false, {Ad, Kd, Kd}, {D, D, D}}, {false, {D}, {Ad}}, {false, {F, F}, {D, D}},
-                          {false, {D}, {F}}, {false, {F}, {D}}, {true, {D, D}, {F, F}},
-                          {false, {Ad}, {D}}, {true, {D, D, D}, {Ad, Kd, Kd}}};
-    for (const Prod& p : prods) {
-      TGemm3Args g = p.shape(M);
-      train_gemm3_plan(g);
-      if (g.ksplit > 1) t.kpart_floats = std::max(t.kpart_floats, g.ksplit * M * (int64_t)g.ncols);
-    }
-  } else {
-    // every (N, K) the layer passes multiply
-    const int64_t shapes[][2] = {{A * d, D}, {KV * d, D}, {D, A * d}, {D, KV * d}, {F, D}, {D, F}};
-    for (const auto& nk : shapes) {
-      const KSplit ks = k_split(M, nk[0], nk[1]);
-      if (ks.ns > 1) t.kpart_floats = std::max(t.kpart_floats, ks.ns * M * nk[0]);
-    }
+  // every (N, K) the layer passes multiply
+  const int64_t shapes[][2] = {{A * d, D}, {KV * d, D}, {D, A * d}, {D, KV * d}, {F, D}, {D, F}};
+  for (const auto& nk : shapes) {
+    const KSplit ks = k_split(M, nk[0], nk[1]);
+    if (ks.ns > 1) t.kpart_floats = std::max(t.kpart_floats, ks.ns * M * nk[0]);
   }
   t.kpart = take(t.kpart_floats);
+  t.hh = take(M * F);
+  t.u = take(M * D);
+  t.u2 = take(M * D);
+  t.end = off;
   t.total = off;
   return t;
 }
@@ -229,7 +211,7 @@ struct TrainRun {
     const KSplit ks = k_split(M, N_, K);
     g.ksplit = 1;
     g.kpiece = K;
-    if (ks.ns > 1 && ks.ns * M * N_ <= Lw.kpart_floats) {
+    if (ks.ns > 1 && !train_small_product(M, N_, K) && ks.ns * M * N_ <= Lw.kpart_floats) {
       g.ksplit = ks.ns;
       g.kpiece = ks.kpiece;
       g.part = f(Lw.kpart);
@@ -249,9 +231,10 @@ struct TrainRun {
 
   // The products of `ops` that share a launch: their own outputs from one A
   // (ksegs = false), or one output, the sum of the products (ksegs = true);
-  // R is added to the (one) output.
-  hipError_t products(std::initializer_list<Op> ops, bool ksegs, int32_t bl, const float* R = nullptr,
-                      const float* ascale = nullptr, int32_t kg = 1) const {
+  // R is added to the (one) output; `sl` holds no operand or output of the
+  // launch and nothing that a later one reads.
+  hipError_t products(std::initializer_list<Op> ops, bool ksegs, int32_t bl, Slices sl,
+                      const float* R = nullptr, const float* ascale = nullptr, int32_t kg = 1) const {
     hipError_t e = hipSuccess;
     if (!bf16) {
       const Op* first = ops.begin();
@@ -282,9 +265,8 @@ struct TrainRun {
     g.astride = (int64_t)c.n_layers * U;
     g.S = (int32_t)S;
     g.kg = kg;
-    train_gemm3_plan(g);
-    if (g.ksplit > 1 && g.ksplit * M * (int64_t)g.ncols > Lw.kpart_floats) return hipErrorInvalidValue;
-    g.part = f(Lw.kpart);
+    train_gemm3_plan(g, sl.floats());
+    g.part = f(sl.at);
     return launch_train_gemm3(g, bl, st);
   }
 
@@ -316,24 +298,24 @@ struct TrainRun {
                                fl(Lw.r1, l), st)) != hipSuccess) return e;
     if ((e = products({{f(Lw.u), D, w.wq, D, fl(Lw.q, l), A * d, D},
                        {f(Lw.u), D, w.wk, D, fl(Lw.k, l), KV * d, D},
-                       {f(Lw.u), D, w.wv, D, fl(Lw.v, l), KV * d, D}}, false, 0)) != hipSuccess) return e;
+                       {f(Lw.u), D, w.wv, D, fl(Lw.v, l), KV * d, D}}, false, 0, {Lw.du, Lw.u})) != hipSuccess) return e;
     if ((e = launch_train_rope(fl(Lw.q, l), A * d, (int32_t)A, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
     if ((e = launch_train_rope(fl(Lw.k, l), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, 1.f, st)) != hipSuccess) return e;
     TAttnArgs a = attn_args(l);
     a.out = fl(Lw.o, l);
     if ((e = launch_train_attn(a, (int32_t)d, B, 0, st)) != hipSuccess) return e;
     // X1 = X_l + (M . O) Wo^T
-    if ((e = products({{fl(Lw.o, l), A * d, w.wo, A * d, fl(Lw.x1, l), D, A * d}}, false, 0, xs(l), ms,
-                      (int32_t)(A / U * d))) != hipSuccess) return e;
+    if ((e = products({{fl(Lw.o, l), A * d, w.wo, A * d, fl(Lw.x1, l), D, A * d}}, false, 0,
+                      {Lw.du, Lw.end}, xs(l), ms, (int32_t)(A / U * d))) != hipSuccess) return e;
     if ((e = launch_train_norm(fl(Lw.x1, l), w.ffn_norm, c.rms_eps, M, (int32_t)D, bf16, f(Lw.u2),
                                fl(Lw.r2, l), st)) != hipSuccess) return e;
     if ((e = products({{f(Lw.u2), D, w.w_gate, D, fl(Lw.ag, l), F, D},
-                       {f(Lw.u2), D, w.w_up, D, fl(Lw.ae, l), F, D}}, false, 0)) != hipSuccess) return e;
+                       {f(Lw.u2), D, w.w_up, D, fl(Lw.ae, l), F, D}}, false, 0, {Lw.du, Lw.u2})) != hipSuccess) return e;
     if (out) {
       if ((e = launch_train_swiglu(fl(Lw.ag, l), fl(Lw.ae, l), M * F, f(Lw.hh), st)) != hipSuccess) return e;
       // X_{l+1} = X1 + (M . H) Wd^T
-      if ((e = products({{f(Lw.hh), F, w.w_down, F, out, D, F}}, false, 0, fl(Lw.x1, l), ms,
-                        (int32_t)(F / U))) != hipSuccess) return e;
+      if ((e = products({{f(Lw.hh), F, w.w_down, F, out, D, F}}, false, 0, {Lw.du, Lw.hh},
+                        fl(Lw.x1, l), ms, (int32_t)(F / U))) != hipSuccess) return e;
     }
     return hipSuccess;
   }
@@ -348,17 +330,17 @@ struct TrainRun {
     const float2* tab = reinterpret_cast<const float2*>(ws + Lw.rope);
     hipError_t e;
     // FFN branch: dHm = dX2 Wd, then SwiGLU (gate / up gradients replace AG / AE)
-    if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1)) != hipSuccess) return e;
+    if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1, {Lw.dO, Lw.end})) != hipSuccess) return e;
     if ((e = launch_train_swiglu_bwd(f(Lw.dh), fl(Lw.ag, l), fl(Lw.ae, l), ms, mstride,
                                      (int32_t)S, M, (int32_t)F, U, f(Lw.pf), st)) != hipSuccess) return e;
     if ((e = products({{fl(Lw.ag, l), F, w.w_gate, D, f(Lw.du), D, F},
-                       {fl(Lw.ae, l), F, w.w_up, D, f(Lw.du), D, F}}, true, 1)) != hipSuccess) return e;
+                       {fl(Lw.ae, l), F, w.w_up, D, f(Lw.du), D, F}}, true, 1, {Lw.dx1, Lw.end})) != hipSuccess) return e;
     if ((e = launch_train_norm_bwd(fl(Lw.x1, l), w.ffn_norm, fl(Lw.r2, l), f(Lw.du), dX2, M, (int32_t)D,
                                    bf16, f(Lw.dx1), st)) != hipSuccess) return e;
     // attention branch: dOm = dX1 Wo, scaled in place by the masks into dO
     float* dO = f(Lw.dO);
     float* dQ = f(Lw.dq);
-    if ((e = products({{f(Lw.dx1), D, w.wo, A * d, dO, A * d, D}}, false, 1)) != hipSuccess) return e;
+    if ((e = products({{f(Lw.dx1), D, w.wo, A * d, dO, A * d, D}}, false, 1, {Lw.dq, Lw.end})) != hipSuccess) return e;
     if ((e = launch_train_attn_mask_bwd(dO, fl(Lw.o, l), ms, mstride, (int32_t)S, M, (int32_t)(A * d),
                                         U, f(Lw.pa), st)) != hipSuccess) return e;
     TAttnArgs a = attn_args(l);
@@ -372,7 +354,7 @@ struct TrainRun {
     if ((e = launch_train_rope(f(Lw.dk), KV * d, (int32_t)KV, (int32_t)d, (int32_t)S, M, tab, -1.f, st)) != hipSuccess) return e;
     if ((e = products({{dQ, A * d, w.wq, D, f(Lw.du), D, A * d},
                        {f(Lw.dk), KV * d, w.wk, D, f(Lw.du), D, KV * d},
-                       {f(Lw.dv), KV * d, w.wv, D, f(Lw.du), D, KV * d}}, true, 1)) != hipSuccess) return e;
+                       {f(Lw.dv), KV * d, w.wv, D, f(Lw.du), D, KV * d}}, true, 1, {Lw.dvec, Lw.end})) != hipSuccess) return e;
     if ((e = launch_train_norm_bwd(xs(l), w.attn_norm, fl(Lw.r1, l), f(Lw.du), f(Lw.dx1), M,
                                    (int32_t)D, bf16, dX, st)) != hipSuccess) return e;
     return launch_train_mask_reduce(f(Lw.pa), f(Lw.pf), B, (int32_t)S, U, c.n_layers, l, f(Lw.dM), st);

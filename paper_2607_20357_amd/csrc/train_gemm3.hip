@@ -286,12 +286,13 @@ __global__ void train_reduce3_kernel(TGemm3Args a) {
 // K pieces of a launch: a piece is one round of a CU, so the launch costs
 // (rounds of 256 workgroups) x (K steps of a piece + about 5 steps to fill and
 // drain the tile), and a split adds the slices' traffic.
-KPieces train_gemm3_pieces(int64_t M, int64_t mtiles_x_ntiles, int64_t ncols, int64_t nchunks) {
+KPieces train_gemm3_pieces(int64_t M, int64_t mtiles_x_ntiles, int64_t ncols, int64_t nchunks,
+                           int64_t slice_floats) {
   KPieces best{1, nchunks};
   double best_t = -1.0;
   for (int64_t ns = 1; ns <= 8; ++ns) {
     const int64_t cp = (nchunks + ns - 1) / ns;
-    if (ns > 1 && (cp < 8 || cp * (ns - 1) >= nchunks)) break;
+    if (ns > 1 && (cp < 8 || cp * (ns - 1) >= nchunks || ns * M * ncols > slice_floats)) break;
     const double rounds = (double)((mtiles_x_ntiles * ns + 255) / 256);
     // a step takes about 0.9 us; slices are written and read at about 4 TB/s
     double t = rounds * (double)(cp + 5) * 0.9;
@@ -304,7 +305,7 @@ KPieces train_gemm3_pieces(int64_t M, int64_t mtiles_x_ntiles, int64_t ncols, in
   return best;
 }
 
-void train_gemm3_plan(TGemm3Args& a) {
+void train_gemm3_plan(TGemm3Args& a, int64_t slice_floats) {
   a.mtiles = (int32_t)((a.M + G3_BM - 1) / G3_BM);
   a.ntn = 0;
   a.ncols = 0;
@@ -320,7 +321,8 @@ void train_gemm3_plan(TGemm3Args& a) {
     }
     a.nchunks = a.ksegs ? a.nchunks + g.chunks : g.chunks;
   }
-  const KPieces kp = train_gemm3_pieces(a.M, (int64_t)a.mtiles * a.ntn, a.ncols, a.nchunks);
+  const KPieces kp = train_gemm3_pieces(a.M, (int64_t)a.mtiles * a.ntn, a.ncols, a.nchunks,
+                                        slice_floats);
   a.ksplit = kp.ns;
   a.cpiece = (int32_t)kp.chunks;
   a.ntiles = a.mtiles * a.ntn * a.ksplit;

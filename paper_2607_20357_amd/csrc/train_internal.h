@@ -87,7 +87,8 @@ struct KPieces {
   int32_t ns;
   int64_t chunks;
 };
-void train_gemm3_plan(TGemm3Args& a);
+// Pieces whose slices fit `slice_floats`.
+void train_gemm3_plan(TGemm3Args& a, int64_t slice_floats);
 hipError_t launch_train_gemm3(const TGemm3Args& a, int32_t bl, hipStream_t st);
 
 // Attention of one layer over B samples of S rows (buffers [B S][heads d]).

@@ -500,3 +500,21 @@ def test_every_workspace_layout_reserves_the_status_word():
         cfg = svl.make_config(w.shape)
         n = svl.svl_workspace_bytes(cfg, w.batch, w.batch * (w.n_vision + w.n_text))
         assert n >= 256 and n % 256 == 0, name
+
+
+@pytest.mark.parametrize("shape,dtype,rows,nbytes", [
+    ("llava7b", "bf16", 9, 5686528), ("llava7b", "bf16", 640, 312474368),
+    ("llava7b", "bf16", 1500, 683209728), ("llava13b", "bf16", 640, 391158528),
+    ("gqa7b", "bf16", 160, 104001280), ("gqa7b", "bf16", 1, 804096),
+    ("llava7b", "f32", 640, 312474368), ("tiny", "f32", 80, 2301952)])
+def test_train_workspace_bytes_values(shape, dtype, rows, nbytes):
+    """The required training workspace of two layers, four units: a buffer of
+    this size is accepted, so the figures stay.  (How a product splits K is
+    no part of it: the slices of its pieces go where they fit.)"""
+    dims = {"llava7b": (4096, 32, 32, 128, 11008), "llava13b": (5120, 40, 40, 128, 13824),
+            "gqa7b": (3584, 28, 4, 128, 18944), "tiny": (256, 4, 4, 64, 688)}[shape]
+    cfg = svl.make_config(None, n_layers=2, n_groups=4, rms_eps=1e-6, rope_theta=10000.0, dtype=dtype,
+                          compute="f16", **dict(zip(("d_model", "n_heads", "n_kv_heads", "head_dim",
+                                                     "d_ffn"), dims)))
+    prm = svl.svl_train_params(0.7, 1.3, 1, 4)
+    assert svl.svl_train_workspace_bytes(cfg, prm, 1, rows - 1, 1) == nbytes

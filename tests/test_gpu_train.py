@@ -219,3 +219,38 @@ def test_train_f32_product_tiles(batch, n_vision, n_text, d_model, d_ffn):
     w = dataclasses.replace(base, shape=shape, n_vision=n_vision, n_text=n_text,
                             name=f"train_f32_b{batch}_{n_vision}_{n_text}_{d_model}")
     _run(w, 14, 1, 4, noise=False)
+
+
+@pytest.mark.parametrize("d_model,heads,kv,head_dim,d_ffn,batch,n_vision,n_text", [
+    (320, 3, 1, 64, 768, 1, 100, 27), (1024, 8, 2, 128, 2816, 2, 40, 9),
+    (4096, 32, 32, 128, 11008, 1, 90, 10), (3584, 28, 4, 128, 18944, 1, 1, 0)])
+def test_train_required_workspace_same_bits(d_model, heads, kv, head_dim, d_ffn, batch, n_vision, n_text):
+    """The slices of a bf16 product's K pieces lie in regions that are dead at
+    its launch.  A step in the required bytes, which runs each forward again
+    before its backward, gives the bits of one that keeps every layer's set,
+    whatever the workspace held before."""
+    base = _tiny(batch)
+    units = 1 if heads == 3 else 4
+    shape = dataclasses.replace(base.shape, n_layers=2, d_model=d_model, n_heads=heads, n_kv_heads=kv,
+                                head_dim=head_dim, d_ffn=d_ffn, n_groups=units, dtype="bf16")
+    w = dataclasses.replace(base, shape=shape, n_vision=n_vision, n_text=n_text, name="train_slices")
+    print(f"train workspace {d_model} {heads}/{kv}x{head_dim} {d_ffn} {batch}x({n_vision}+{n_text})",
+          flush=True)
+    cfg = svl.make_config(shape)
+    vision, text = W.draw_hidden(w, 15, device="cuda")
+    layers = svl.LayerTable([W.draw_layer_weights(w, l, 15, device="cuda") for l in range(2)])
+    rng = np.random.default_rng(15)
+    t = lambda *sh: torch.from_numpy(rng.standard_normal(sh).astype(np.float32)).cuda()
+    z, g, G = t(batch, n_vision), t(batch, units), t(batch, n_vision + n_text, d_model)
+    prm = svl.svl_train_params(0.5, 0.5, 1, units)
+    full = svl.alloc_train_workspace(cfg, prm, batch, n_vision, n_text)
+    small = svl.svl_train_workspace_bytes(cfg, prm, batch, n_vision, n_text)
+    assert small < full.numel()
+    outs = []
+    for ws, fill in ((full, 0), (full, 255), (full[:small], 255)):
+        ws.fill_(fill)
+        outs.append(svl.svl_train_step(cfg, layers, prm, z, g, vision, text, G, ws))
+    torch.cuda.synchronize()
+    for o in outs[1:]:
+        for k in o:
+            assert torch.equal(o[k], outs[0][k]), k
