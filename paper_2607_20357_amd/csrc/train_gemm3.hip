@@ -241,6 +241,7 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
                    : a.seg[sn].C;
   const int64_t ldc = split ? a.ncols : a.seg[sn].ldc;
   const float* R = split ? nullptr : a.R;
+  uint64_t nans = 0;                             // bit 16 j + 4 i + r: total[i][j][r] is a NaN
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int col = n0 + 64 * wn + 16 * j + (lane & 15);
@@ -252,8 +253,92 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
         const int row = 64 * wm + 16 * i + 4 * (lane >> 4) + r;
         if (row >= rows) continue;
         float o = total[i][j][r];
+        if (o != o) nans |= uint64_t(1) << (16 * j + 4 * i + r);
         if (R) o += R[(m0 + row) * a.ldr + col];
         C[(m0 + row) * ldc + col] = o;
+      }
+  }
+  if (__builtin_expect(!__any(nans != 0), 1)) return;
+
+  // NaNs: an infinite weight times a middle or low term of zero is one, where
+  // the float32 product is infinite.  If the wave's weights hold a value that is
+  // not finite, those outputs are formed again as float32 products
+  // (v_mfma_f32_16x16x4_f32, operands straight from memory; lane group q takes
+  // k = 8 q + [0, 8) of every 32, in the same order for both operands).  A step
+  // of two layers, 7B shape, 640 rows, takes 4.5 ms, one whose every value is NaN
+  // 11.9 (15.7 as float32 products).
+  const int col = n0 + 64 * wn + (lane & 15);
+  auto segment = [&](int c, int& k) -> const TSeg& {   // of K step c; k: the lane's first
+    int s = sn;
+    if (a.ksegs) {
+      s = 0;
+      while (s + 1 < a.nseg && c >= a.seg[s].chunks) c -= a.seg[s++].chunks;
+    }
+    k = c * G3_BK + 8 * (lane >> 4);
+    return a.seg[s];
+  };
+  auto weights = [&](const TSeg& g, int k, int j, uint32_t (&w)[8]) __attribute__((always_inline)) {
+    const bool in = k < g.K && col + 16 * j < N;
+    const uint16_t* p = static_cast<const uint16_t*>(g.B) +
+                        (in ? (BL == 0 ? (col + 16 * j) * g.ldb + k : k * g.ldb + col + 16 * j) : 0);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) w[e] = in ? (uint32_t)p[BL == 0 ? e : e * g.ldb] << 16 : 0u;
+  };
+  bool special = false;
+#pragma unroll 2
+  for (int c = c_lo; c < c_hi; ++c) {
+    int k;
+    const TSeg& g = segment(c, k);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      uint32_t w[8];
+      weights(g, k, j, w);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) special |= (w[e] & 0x7f800000u) == 0x7f800000u;
+    }
+  }
+  if (!__any(special)) return;
+  for (int i = 0; i < 4; ++i) {
+    // bit 4 j + r: the lane's NaNs in the four blocks of row block i
+    uint32_t bits = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bits |= ((uint32_t)(nans >> (16 * j + 4 * i)) & 15u) << (4 * j);
+    if (!__any(bits != 0)) continue;
+    const int arow2 = 64 * wm + 16 * i + (lane & 15);
+    const float* scale = ASC && arow2 < rows ? a.ascale + (m0 + arow2) / a.S * a.astride : nullptr;
+    floatx4 sum[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) sum[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    for (int c = c_lo; c < c_hi; ++c) {
+      int k;
+      const TSeg& g = segment(c, k);
+      float x[8] = {};
+      uint32_t w[4][8];
+      if (k < g.K && arow2 < rows) {
+        const float* p = g.A + (m0 + arow2) * g.lda + k;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          x[e] = p[e];
+          if constexpr (ASC) x[e] *= scale[(uint32_t)(k + e) / (uint32_t)a.kg];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) weights(g, k, j, w[j]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], __uint_as_float(w[j][e]), sum[j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if (!(bits >> (4 * j + r) & 1)) continue;
+        const int64_t row = m0 + 64 * wm + 16 * i + 4 * (lane >> 4) + r;
+        float o = sum[j][r];
+        if (R) o += R[row * a.ldr + col + 16 * j];
+        C[row * ldc + col + 16 * j] = o;
       }
   }
 }

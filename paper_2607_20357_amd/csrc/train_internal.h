@@ -74,7 +74,7 @@ struct TGemm3Args {
   int32_t nseg;
   bool ksegs;
   int64_t M;
-  const float* R;       // nullptr, or added to C (one output; may equal it)
+  const float* R;       // nullptr, or added to C (one output, another array)
   int64_t ldr;
   const float* ascale;  // as in TGemmArgs (nseg == 1)
   int64_t astride;

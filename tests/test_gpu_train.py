@@ -254,3 +254,47 @@ def test_train_required_workspace_same_bits(d_model, heads, kv, head_dim, d_ffn,
     for o in outs[1:]:
         for k in o:
             assert torch.equal(o[k], outs[0][k]), k
+
+
+@pytest.mark.parametrize("name", ["w_down", "w_up", "text"])
+def test_train_bf16_infinite_weight(name):
+    """One infinite bf16 weight: its output column is +inf or -inf by the sign
+    of the row's factor, as a float32 product gives it (a factor's zero low
+    term, one in about 256, times infinity would be NaN); and an infinite
+    column of the activations makes every output infinite.  A NaN input alone
+    ("text") makes its row and the later rows of its sample NaN."""
+    base = _tiny(2)
+    shape = dataclasses.replace(base.shape, n_layers=1, d_model=320, n_heads=4, n_kv_heads=2, head_dim=64,
+                                d_ffn=768, n_groups=4, dtype="bf16")
+    w = dataclasses.replace(base, shape=shape, n_vision=0, n_text=700, name="train_inf_weight")
+    cfg = svl.make_config(shape)
+    vision, text = W.draw_hidden(w, 16, device="cuda")
+    layer = dict(W.draw_layer_weights(w, 0, 16, device="cuda"))
+    if name == "text":
+        text[1, 400, 7] = float("nan")
+    else:
+        layer[name] = layer[name].clone()
+        layer[name][300, 129] = float("inf")    # [out][in]
+    prm = svl.svl_train_params(0.5, 0.5, 1, 4)
+    ws = svl.alloc_train_workspace(cfg, prm, 2, 0, 700)
+    z, g = torch.zeros(2, 0, device="cuda"), torch.zeros(2, 0, device="cuda")
+    out = svl.svl_train_step(cfg, svl.LayerTable([layer]), prm, z, g, vision, text, None, ws)
+    torch.cuda.synchronize()
+    hidden = out["hidden"].cpu().numpy()
+    hl = host_layer(layer)
+    for b in range(2):
+        with np.errstate(all="ignore"):
+            ref, _ = ot.masked_forward(shape, lambda l: hl, W.as_f32(vision)[b], W.as_f32(text)[b],
+                                       np.zeros(0), np.zeros((0, 4)), 1, 4)
+        if name == "w_down":
+            assert np.isinf(ref[:, 300]).all()
+            np.testing.assert_array_equal(hidden[b][:, 300], ref[:, 300])
+            cols = np.arange(320) != 300
+            assert _normwise(hidden[b][:, cols], ref[:, cols]) <= TOL_HIDDEN
+        elif name == "text":
+            # (the oracle's masked probabilities, 0 times NaN, reach earlier rows too)
+            assert np.isfinite(hidden[b][:384]).all()
+            assert np.isnan(hidden[b][400:]).all() if b else np.isfinite(hidden[b]).all()
+        else:
+            assert np.isinf(ref).all()
+            np.testing.assert_array_equal(hidden[b], ref)
