@@ -266,7 +266,10 @@ struct Exec {
       a.pld = ldo;
       a.pslice = L.partial_slice;
     }
-    hipError_t e = timed(cls, st, [&] { return launch_gemm_mfma(a, epi, g.nb, g.waves, f16, st); });
+    hipError_t e = timed(cls, st, [&] {
+      return a.A2 && g.apart ? launch_gemm_lo(a, epi, g.nb, st)
+                             : launch_gemm_mfma(a, epi, g.nb, g.waves, f16, st);
+    });
     if (e != hipSuccess || !(paired && g.nsplit > 1)) return e;
     FinishArgs f{};
     f.groups = a.groups;

@@ -20,12 +20,11 @@
 // MFMAs per fragment pair leaves the matrix pipes as the larger part of a
 // stage.
 //
-// Against eight waves that each load and multiply (same box, both in turn; a
-// LLaVA-7B prefill of 350 rows, 3 of 4 groups on): eight layers 2.65 -> 2.23
-// ms; one layer of six samples of 54-90 rows, whose tiles leave each wave one
-// row block, 570 -> 583 us.  The single-term products (fp16) have half the
-// MFMAs per byte loaded and measured 5% slower in this form, so they keep
-// theirs.
+// Against eight waves that each load and multiply (a LLaVA-7B prefill of 350
+// rows, 3 of 4 groups on): eight layers 2.65 -> 2.23 ms.  Launches where that
+// form is the faster one keep it (waves_apart, plan_types.h).  The single-term
+// products (fp16) have half the MFMAs per byte loaded and measured 5% slower in
+// this form, so they keep theirs.
 #include <type_traits>
 #include <utility>
 
@@ -60,7 +59,11 @@ template <int EPI, int NB>
 __global__ __launch_bounds__(512) void gemm_lo_kernel(MmArgs a) {
   constexpr int NT = 512;
   constexpr int CW = 4;                         // multiplying waves
-  constexpr int RB = BM / (16 * CW);            // 16-row blocks per multiplying wave
+  // 16-row blocks per multiplying wave; tiles of 8 blocks come with up to 12 row
+  // blocks in all (a fourth per wave would spill registers)
+  constexpr int RB = NB == 8 ? 3 : BM / (16 * CW);
+  static_assert(NB != 8 || !(waves_apart(8, 13) || waves_apart(8, 14) || waves_apart(8, 15) ||
+                             waves_apart(8, 16)), "the planner's rule");
   constexpr int LT = 256;                       // threads that bring the weights
   constexpr int BN = NB * 16;                   // weight rows per tile
   // weight register stages in flight (8 NB registers each)
@@ -183,8 +186,9 @@ __global__ __launch_bounds__(512) void gemm_lo_kernel(MmArgs a) {
     constexpr int AF = 2;                       // fragments per row block and k-step: high, low
     constexpr int NG = NB == 8 ? 4 : 1;         // weight fragment groups per k-step
     constexpr int GB = NB / NG;
-    // registers for the accumulators, two fragment groups and the A slots
-    constexpr int FREE = 212 - 4 * NB * NRB - 8 * GB;
+    // registers for the accumulators, two fragment groups and the A slots (more
+    // spill at 8 blocks)
+    constexpr int FREE = (NB == 8 ? 204 : 212) - 4 * NB * NRB - 8 * GB;
     constexpr int SLOT = 4 * (NRB > 0 ? NRB : 1) * AF;
     constexpr int NSK = FREE >= 8 * SLOT   ? 8
                         : FREE >= 6 * SLOT ? 6
@@ -311,8 +315,8 @@ __global__ __launch_bounds__(512) void gemm_lo_kernel(MmArgs a) {
   if (nk > 0) {
     const int nrb = ((mcnt + 15) / 16 - wave + CW - 1) / CW;   // row blocks w, w + 4, .. in the tile
     if (wave >= CW) bring();
-    else if (nrb >= 4) multiply(std::integral_constant<int, 4>{});
-    else if (nrb == 3) multiply(std::integral_constant<int, 3>{});
+    else if (nrb >= 4 && RB >= 4) multiply(std::integral_constant<int, RB>{});
+    else if (nrb >= 3) multiply(std::integral_constant<int, 3>{});
     else if (nrb == 2) multiply(std::integral_constant<int, 2>{});
     else if (nrb == 1) multiply(std::integral_constant<int, 1>{});
     else multiply(std::integral_constant<int, 0>{});

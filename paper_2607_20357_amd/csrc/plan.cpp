@@ -177,6 +177,7 @@ struct MmBuild {
     L.ngroups = (int32_t)groups.size();
     L.ntiles = (int32_t)count;
     L.nb = nb;
+    L.apart = waves_apart(nb, cdiv(std::min(MFMA_BM, max_rows), 16));
     L.nsplit = nsplit;
     return L;
   }

@@ -148,6 +148,25 @@ constexpr int MFMA_BM = 256, MFMA_BK = 64;
 constexpr int MFMA_MAX_SPLIT = 8;
 constexpr int MFMA_MAX_NB = 8;
 constexpr int MFMA_PARTIAL_ROWS = 4096;   // split pieces x rows the partial buffer holds
+// Two-term bf16 products (QKV, gate/up) of tiles of `nb` blocks and up to `rb`
+// 16-row blocks: whether waves that load and waves that multiply are apart
+// (gemm_lo_kernel) or every wave does both (gemm_mfma_kernel).  Apart, the
+// busiest SIMD multiplies ceil(rb / 4) row blocks of a tile; together
+// min(rb, 2), and from 9 on 3 (9) or 4 (10 and more).  Where that is fewer
+// (rb 2-4 and 10-12), apart is faster at every nb; where it is equal it depends
+// on how many chunks of A the other form keeps in flight (four up to nb 4, two
+// above) and on what each spills (nb 8).  Time together / time apart per launch, three
+// model widths, 1-8 samples of 16-300 rows:
+//   nb 2     rb 1 1.01, 2-4 1.03-1.19, 5 0.97-0.98, 6-9 0.95-1.04, 10-16 1.00-1.12
+//   nb 3-4   rb 1 0.99, 2-4 0.98-1.06, 5-9 0.92-1.03 (mean 0.97), 10-16 1.00-1.16
+//   nb 5-6   1.04-1.70
+//   nb 8     rb 1-4 1.24-1.36, 5-8 1.00-1.09, 9 0.92-0.93, 10-12 1.02-1.09, 13-16 0.94-1.02 (mean 0.98)
+inline constexpr bool waves_apart(int32_t nb, int32_t rb) {
+  if (nb > 6) return rb <= 8 || (rb >= 10 && rb <= 12);
+  if (nb > 4) return true;
+  return nb > 2 ? rb < 5 || rb > 9 : rb != 5;
+}
+
 constexpr int F32_BM = 32, F32_BN = 32;
 constexpr int F32_SWIGLU_CH = 16;
 constexpr int ATTN_BQ = 64;          // query rows per attention workgroup

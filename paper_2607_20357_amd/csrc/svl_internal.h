@@ -197,7 +197,8 @@ hipError_t launch_resid_norm(const NormArgs& a, int32_t out_kind, hipStream_t st
 // waves: 8 (any epilogue and block count) or 4 (EPI_RESID with 4 blocks)
 hipError_t launch_gemm_mfma(const MmArgs& a, int32_t epi, int32_t nb, int32_t waves, bool f16,
                             hipStream_t st);
-// bf16 QKV / gate-up with the activations' low parts (a.A2)
+// bf16 QKV / gate-up with the activations' low parts (a.A2), loading and multiplying
+// waves apart; launch_gemm_mfma takes them too, with every wave doing both
 hipError_t launch_gemm_lo(const MmArgs& a, int32_t epi, int32_t nb, hipStream_t st);
 hipError_t launch_finish(const FinishArgs& a, int32_t epi, bool f16, hipStream_t st);
 // Decode: one-row groups, one workgroup per 16-column block (QKV, SWIGLU, RESID).

@@ -167,6 +167,16 @@ static void check_prefill(const Case& c) {
           }
         }
     }
+    // two-term products: the form goes by the launch's block count and its tallest
+    // tile (gemm_lo_kernel holds what the rule gives it)
+    for (const GemmLaunch* g : {&LP.qkv, &LP.gu}) {
+      const MmTile* tl = at<MmTile>(plan, g->tiles_off);
+      int rb = 0;
+      for (int t = 0; t < g->ntiles; ++t) rb = std::max(rb, (tl[t].mcnt + 15) / 16);
+      if (g->ntiles > 0)
+        CHECK(g->apart == waves_apart(g->nb, rb), "form of a launch of %d blocks, %d row blocks",
+              g->nb, rb);
+    }
     // ---- gate/up
     {
       std::map<std::pair<int, int>, int> cg;
