@@ -246,10 +246,14 @@ struct MmBuild {
   }
   // Output and down projections: 4-block tiles; a launch whose tiles would
   // leave half of the CUs idle or more splits K into float32 partial slices
-  // (at least 2 chunks per piece, the slices within the partial buffer).  The
-  // line is the number of tiles, not the rows of a sample: 350 rows (two M
-  // tiles, 128 tiles of a 4096-wide output) in one piece take 79 us (down) and
-  // 33 us (output), in two 47 and 22 us, and the next norm 4 us more.
+  // (at least 2 chunks per piece, the slices within the partial buffer).
+  // Samples of several M tiles split as far as it pays: a piece saves its
+  // share of the K chunks, about 0.5 us each; its slice is written and read
+  // again at about 4 TB/s, and the next norm takes about 2 us more.  350 rows (two M tiles, 128 tiles of a 4096-wide
+  // output): 79 (down) and 33 us (output) in one piece, 47 and 22 us in two, the
+  // next norm 4 us more.  2048 rows of a 1024-wide layer, half of its groups:
+  // the layer takes 163.8 us in one piece and 170.2 us in two (5 us of chunks
+  // saved, 17 MB of slices); 4000 rows of a 512-wide one 188.1 and 196.6 us.
   GemmLaunch finish_plain(ImageWriter& w, int32_t R, int32_t D, int64_t cap_floats,
                           bool rowvec = false) {
     int32_t s = 1;
@@ -260,6 +264,17 @@ struct MmBuild {
       s = std::min(s, MFMA_MAX_SPLIT);
       s = std::min(s, std::max(1, min_chunks / 2));
       s = std::min<int64_t>(s, std::max<int64_t>(1, cap_floats / ((int64_t)std::max(1, R) * D)));
+      if (max_rows > kSkinnyRows) {
+        int64_t rows = 0;
+        for (const auto& g : groups) rows += g.nrows;
+        int32_t best = 1;
+        double best_us = 2.0;
+        for (int32_t p = 2; p <= s; ++p) {
+          const double us = 0.5 * max_chunks * (1.0 - 1.0 / p) - 2.0 * p * (double)rows * D * 4.0 / 4.0e6;
+          if (us > best_us) { best = p; best_us = us; }
+        }
+        s = best;
+      }
     }
     GemmLaunch L = finish(w, 4, 4, s);
     // more tiles than CUs: 4-wave tiles, two per CU (measured 20% faster per

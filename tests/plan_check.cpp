@@ -269,6 +269,38 @@ static void check_prefill(const Case& c) {
   }
 }
 
+// K pieces of the output and down projections of one layer, `groups` of 4 head
+// groups and FFN slices on.
+static void check_split(int D, int F, int rows, int B, int groups, int want_o, int want_down) {
+  Case c{};
+  c.cfg.dtype = SVL_BF16;
+  c.cfg.n_layers = 1;
+  c.cfg.d_model = D;
+  c.cfg.n_heads = c.cfg.n_kv_heads = D / 128;
+  c.cfg.head_dim = 128;
+  c.cfg.d_ffn = F;
+  c.cfg.n_groups = 4;
+  c.cfg.rms_eps = 1e-6f;
+  c.cfg.rope_theta = 1e4f;
+  c.B = B;
+  c.seq.assign(B, rows);
+  c.lon.assign(B, 1);
+  c.ffn_gated = true;
+  const int A = c.cfg.n_heads;
+  for (int b = 0; b < B; ++b) {
+    for (int h = 0; h < A; ++h) c.hm.push_back(h / (A / 4) < groups);
+    for (int g = 0; g < 4; ++g) c.fm.push_back(g < groups);
+  }
+  auto masks = masks_of(c);
+  Plan plan;
+  std::string err;
+  CHECK(build_plan(c.cfg, B, c.seq.data(), c.seq.data(), 1, masks.data(), &plan, &err), "%s", err.c_str());
+  const int o = plan.layers[0].o.nsplit, down = plan.layers[0].down.nsplit;
+  CHECK(o == want_o && down == want_down, "D %d rows %d x %d groups %d: output in %d pieces, down in %d", D,
+        B, rows, groups, o, down);
+  if (D <= 512) check_prefill(c);
+}
+
 static void check_decode(const Case& c) {
   const svl_config& cfg = c.cfg;
   const int B = c.B, L = cfg.n_layers, A = cfg.n_heads, KV = cfg.n_kv_heads, d = cfg.head_dim;
@@ -457,6 +489,22 @@ int main() {
     c.ffn_gated = true;
     check_prefill(c);
     ++cases;
+  }
+  // one row tile a sample: as many pieces as CUs are idle; several: as far as
+  // the chunks saved outweigh the slices
+  check_split(4096, 11008, 208, 1, 3, 4, 4);
+  check_split(4096, 11008, 350, 1, 4, 2, 2);
+  check_split(4096, 11008, 350, 1, 2, 2, 2);
+  check_split(4096, 11008, 600, 1, 4, 1, 1);
+  check_split(3584, 18944, 512, 1, 3, 2, 2);
+  check_split(1024, 2816, 2048, 1, 2, 1, 1);
+  check_split(1024, 2816, 2048, 1, 4, 1, 2);
+  check_split(512, 1536, 4000, 1, 2, 1, 1);
+  check_split(512, 1536, 300, 1, 4, 1, 6);
+  check_split(512, 1536, 1024, 1, 2, 1, 1);
+  if (g_fail) {
+    std::fprintf(stderr, "plan_check: %d failures\n", g_fail);
+    return 1;
   }
   if (g_waves4 == 0) {
     std::fprintf(stderr, "plan_check: no case planned 4-wave tiles\n");

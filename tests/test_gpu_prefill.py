@@ -413,3 +413,26 @@ def test_gated_weights_are_never_read():
         poisoned.append(lw)
     got = gpu_prefill(w, inp, poisoned)[2]
     np.testing.assert_array_equal(got, clean)
+
+
+@pytest.mark.parametrize("compute", ["f16", "bf16"])
+def test_prefill_split_over_two_row_tiles(compute):
+    """Output and down projections that split K although the samples span two
+    row tiles (16 column tiles on 256 CUs): four layers of three samples of
+    320 rows at different masks, each skipping one layer, so that float32
+    slices wait over layers that some samples leave out; and one layer where
+    one sample has its attention block off and another its FFN."""
+    import dataclasses
+    w = W.scaled(W.get_workload("llava7b_b8_ragged"), n_layers=4, d_model=1024, n_heads=16,
+                 n_kv_heads=16, d_ffn=2816, batch=3, n_vision=300, n_text=20,
+                 name="two_row_tiles_split")
+    w = dataclasses.replace(w, keep_choices=(1.0, 0.8), groups_keep_choices=(4, 3),
+                            layers_skipped_range=(1, 1))
+    _check_prefill(w, seed=6, compute=compute)
+    head_mask = np.ones((4, 16), np.uint8)
+    ffn_mask = np.ones((4, 4), np.uint8)
+    head_mask[0] = 0
+    ffn_mask[1] = 0
+    errs = _layer_case(w.shape, np.array([300, 257, 40, 0], np.int32), np.ones(4, np.uint8), head_mask,
+                       ffn_mask, compute=compute)
+    assert max(errs) <= tol_for(w.shape), errs
