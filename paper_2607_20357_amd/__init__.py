@@ -13,5 +13,5 @@ from .binding import (  # noqa: F401
     svl_prefill_controlled, svl_select_tokens, svl_timing_enable, svl_timing_read,
     svl_workspace_bytes, alloc_train_workspace, svl_train_params, svl_train_step,
     SVL_STATUS_NONFINITE, svl_workspace_status,
-    svl_train_workspace_bytes,
+    svl_train_workspace_bytes, svl_train_workspace_bytes_full,
 )

@@ -699,17 +699,47 @@ def svl_train_workspace_bytes(cfg: svl_config, params: svl_train_params, batch: 
     return int(n)
 
 
+def svl_train_workspace_bytes_full(cfg: svl_config, params: svl_train_params, batch: int,
+                                   n_vision: int, n_text: int) -> int:
+    """Bytes with which a step keeps every layer's forward intermediates (the
+    required bytes where those would take more than 16 GiB)."""
+    n = load_library().svl_train_workspace_bytes_full(ctypes.byref(cfg), ctypes.byref(params),
+                                                      int(batch), int(n_vision), int(n_text))
+    if n == 0:
+        raise SvlError(2, "svl_train_workspace_bytes_full: " +
+                       load_library().svl_last_error().decode())
+    return int(n)
+
+
+def _has_room(extra: int, device) -> bool:
+    """Whether `extra` bytes are at most a quarter of what the device has free
+    (with what torch holds and does not use), or a thousandth of all it has
+    (the query of the free memory takes about 150 us)."""
+    device = torch.device(device)
+    if device.type != "cuda":
+        return False
+    if extra <= torch.cuda.get_device_properties(device).total_memory // 1024:
+        return True
+    free = (torch.cuda.mem_get_info(device)[0] + torch.cuda.memory_reserved(device) -
+            torch.cuda.memory_allocated(device))
+    return extra <= free // 4
+
+
 def alloc_train_workspace(cfg: svl_config, params: svl_train_params, batch: int, n_vision: int,
-                          n_text: int, device="cuda") -> torch.Tensor:
-    """Room for every layer's forward intermediates (a step then runs no forward
-    twice), or the required bytes where the device has no memory for that."""
+                          n_text: int, device="cuda", keep_layers: bool = True) -> torch.Tensor:
+    """A training workspace.  With keep_layers it holds every layer's forward
+    intermediates, so that a step runs no forward twice (same results): up to
+    16 GiB more than the required bytes (109 MB a layer at the 7B shape, 640
+    rows), taken only while that is at most a quarter of the device's free
+    memory or a thousandth of all of it.  Otherwise it has the required bytes."""
     n = svl_train_workspace_bytes(cfg, params, batch, n_vision, n_text)
-    full = load_library().svl_train_workspace_bytes_full(ctypes.byref(cfg), ctypes.byref(params),
-                                                         int(batch), int(n_vision), int(n_text))
-    try:
-        return torch.empty(max(n, int(full)), dtype=torch.uint8, device=device)
-    except torch.OutOfMemoryError:
-        return torch.empty(n, dtype=torch.uint8, device=device)
+    full = svl_train_workspace_bytes_full(cfg, params, batch, n_vision, n_text)
+    if keep_layers and full > n and _has_room(full - n, device):
+        try:
+            return torch.empty(full, dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty(n, dtype=torch.uint8, device=device)
 
 
 def svl_train_step(cfg: svl_config, layers, params: svl_train_params, logits: torch.Tensor,

@@ -518,3 +518,39 @@ def test_train_workspace_bytes_values(shape, dtype, rows, nbytes):
                                                      "d_ffn"), dims)))
     prm = svl.svl_train_params(0.7, 1.3, 1, 4)
     assert svl.svl_train_workspace_bytes(cfg, prm, 1, rows - 1, 1) == nbytes
+
+
+def test_train_workspace_leaves_memory_to_the_caller(monkeypatch):
+    """alloc_train_workspace takes the room for every layer's intermediates only
+    where it is asked to and where that is a small part of the free memory."""
+    cfg = svl.make_config(WORKLOADS["tiny_f32"].shape)
+    prm = svl.svl_train_params(0.7, 1.3, 1, 4)
+    need = svl.svl_train_workspace_bytes(cfg, prm, 2, 64, 16)
+    full = svl.svl_train_workspace_bytes_full(cfg, prm, 2, 64, 16)
+    assert full > need
+    assert svl.alloc_train_workspace(cfg, prm, 2, 64, 16, "cpu").numel() == need
+
+    device_of, sizes = {}, []
+    empty = torch.empty
+
+    def fake_empty(n, dtype, device):
+        sizes.append(int(n))
+        if device_of.get("oom") and n > need:
+            raise torch.OutOfMemoryError("no memory")
+        return empty(n, dtype=dtype)
+    monkeypatch.setattr(binding.torch, "empty", fake_empty)
+    class Card:
+        total_memory = 1024 * (full - need) - 1
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: Card)
+    monkeypatch.setattr(torch.cuda, "memory_reserved", lambda d: 3000)
+    monkeypatch.setattr(torch.cuda, "memory_allocated", lambda d: 1000)
+    for free, want in ((4 * (full - need) - 2000, full), (4 * (full - need) - 2004, need), (0, need)):
+        monkeypatch.setattr(torch.cuda, "mem_get_info", lambda d, free=free: (free, 1 << 40))
+        assert svl.alloc_train_workspace(cfg, prm, 2, 64, 16, "cuda").numel() == want
+    Card.total_memory += 1          # a thousandth of the card: taken without asking
+    assert svl.alloc_train_workspace(cfg, prm, 2, 64, 16, "cuda").numel() == full
+    assert svl.alloc_train_workspace(cfg, prm, 2, 64, 16, "cuda", keep_layers=False).numel() == need
+    device_of["oom"] = True
+    sizes.clear()
+    assert svl.alloc_train_workspace(cfg, prm, 2, 64, 16, "cuda").numel() == need
+    assert sizes == [full, need]
