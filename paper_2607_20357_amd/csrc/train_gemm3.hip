@@ -241,7 +241,6 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
                    : a.seg[sn].C;
   const int64_t ldc = split ? a.ncols : a.seg[sn].ldc;
   const float* R = split ? nullptr : a.R;
-  uint64_t nans = 0;                             // bit 16 j + 4 i + r: total[i][j][r] is a NaN
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int col = n0 + 64 * wn + 16 * j + (lane & 15);
@@ -253,12 +252,18 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
         const int row = 64 * wm + 16 * i + 4 * (lane >> 4) + r;
         if (row >= rows) continue;
         float o = total[i][j][r];
-        if (o != o) nans |= uint64_t(1) << (16 * j + 4 * i + r);
         if (R) o += R[(m0 + row) * a.ldr + col];
         C[(m0 + row) * ldc + col] = o;
       }
   }
-  if (__builtin_expect(!__any(nans != 0), 1)) return;
+  bool nan = false;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      nan |= __builtin_isunordered(total[i][j][0], total[i][j][1]) |
+             __builtin_isunordered(total[i][j][2], total[i][j][3]);
+  if (__builtin_expect(!__any(nan), 1)) return;
 
   // NaNs: an infinite weight times a middle or low term of zero is one, where
   // the float32 product is infinite.  If the wave's weights hold a value that is
@@ -298,6 +303,16 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
     }
   }
   if (!__any(special)) return;
+  uint64_t nans = 0;                             // bit 16 j + 4 i + r: total[i][j][r] is a NaN
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (total[i][j][r] != total[i][j][r] && col + 16 * j < N &&
+            64 * wm + 16 * i + 4 * (lane >> 4) + r < rows)
+          nans |= uint64_t(1) << (16 * j + 4 * i + r);
   for (int i = 0; i < 4; ++i) {
     // bit 4 j + r: the lane's NaNs in the four blocks of row block i
     uint32_t bits = 0;
