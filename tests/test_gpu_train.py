@@ -298,3 +298,77 @@ def test_train_bf16_infinite_weight(name):
         else:
             assert np.isinf(ref).all()
             np.testing.assert_array_equal(hidden[b], ref)
+
+
+def _truncated(x, bits):
+    """x as float32 with its significand cut to `bits` (8 per bf16 term)."""
+    v = x.to(torch.float32).contiguous().view(torch.int32)
+    return (v & ~((1 << (24 - bits)) - 1)).view(torch.float32).double()
+
+
+def _forward64(s, layers, x, masks, prefix, units, bits=None):
+    """The masked decoder's forward of one sample in float64 (CPU); with `bits`,
+    every product's activations are cut to that many significand bits."""
+    cut = (lambda t: t) if bits is None else (lambda t: _truncated(t, bits))
+    A, KV, d, S = s.n_heads, s.n_kv_heads, s.head_dim, x.shape[0]
+    w = s.rope_theta ** (-2.0 * torch.arange(d // 2, dtype=torch.float64) / d)
+    phi = torch.arange(S, dtype=torch.float64)[:, None] * w[None, :]
+
+    def rope(a):
+        a1, a2 = a[..., :d // 2], a[..., d // 2:]
+        c, sn = torch.cos(phi)[:, None], torch.sin(phi)[:, None]
+        return torch.cat([a1 * c - a2 * sn, a2 * c + a1 * sn], dim=-1)
+
+    def norm(t, g):
+        return t * torch.rsqrt((t * t).mean(-1, keepdim=True) + s.rms_eps) * g
+    for l, W_ in enumerate(layers):
+        m = torch.ones(units, dtype=torch.float64) if l < prefix else masks[l - prefix]
+        u = cut(norm(x, W_["attn_norm"]))
+        q = rope((u @ W_["wq"].t()).reshape(S, A, d))
+        k = rope((u @ W_["wk"].t()).reshape(S, KV, d)).repeat_interleave(A // KV, 1)
+        v = (u @ W_["wv"].t()).reshape(S, KV, d).repeat_interleave(A // KV, 1)
+        sc = torch.matmul(q.transpose(0, 1), k.permute(1, 2, 0)) / d ** 0.5
+        sc = sc.masked_fill(torch.ones(S, S).triu(1).bool(), -float("inf"))
+        o = torch.matmul(torch.softmax(sc, -1), v.transpose(0, 1).contiguous()).transpose(0, 1)
+        o = (o * m.repeat_interleave(A // units)[None, :, None]).reshape(S, A * d)
+        x = x + cut(o) @ W_["wo"].t()
+        u = cut(norm(x, W_["ffn_norm"]))
+        g = u @ W_["w_gate"].t()
+        h = g * torch.sigmoid(g) * (u @ W_["w_up"].t()) * m.repeat_interleave(s.d_ffn // units)[None, :]
+        x = x + cut(h) @ W_["w_down"].t()
+    return x
+
+
+@pytest.mark.parametrize("batch,rows", [(1, 1), (1, 64), (1, 129), (3, 86)])
+def test_train_bf16_products_keep_all_three_terms(batch, rows):
+    """bf16-weight products at tile edges, close enough to see the third term.
+    Hidden states: float32 sums of up to 768 products in runs of 512, and the
+    float32 norms, softmax and residuals of two layers, about 10 roundings of
+    2^-24 in a row of size one: 6e-7 normwise.  With 16 bits of each factor the
+    products alone are off by 2^-17 of their size, the same way for every
+    factor."""
+    base = _tiny(batch)
+    shape = dataclasses.replace(base.shape, d_model=320, n_heads=3, n_kv_heads=1, head_dim=64,
+                                d_ffn=768, n_groups=3, dtype="bf16")
+    w = dataclasses.replace(base, shape=shape, n_vision=0, n_text=rows, name="train_terms")
+    cfg = svl.make_config(shape)
+    vision, text = W.draw_hidden(w, 17, device="cuda")
+    layers = [W.draw_layer_weights(w, l, 17, device="cuda") for l in range(2)]
+    rng = np.random.default_rng(17)
+    g = torch.from_numpy(rng.normal(0.6, 1.5, (batch, 3)).astype(np.float32)).cuda()
+    prm = svl.svl_train_params(0.7, 1.3, 1, 3)
+    ws = svl.alloc_train_workspace(cfg, prm, batch, 0, rows)
+    out = svl.svl_train_step(cfg, svl.LayerTable(layers), prm, torch.zeros(batch, 0, device="cuda"), g,
+                             vision, text, None, ws)
+    hidden = out["hidden"].double().cpu()
+    hl = [{k: v.double().cpu() for k, v in l.items()} for l in layers]
+    for b in range(batch):
+        masks = (g[b].cpu() > 0).double().reshape(1, 3)
+        x = text[b].double().cpu()
+        ref = _forward64(shape, hl, x, masks, 1, 3)
+        den = ref.abs().max()
+        err = float((hidden[b] - ref).abs().max() / den)
+        two = float((_forward64(shape, hl, x, masks, 1, 3, bits=16) - ref).abs().max() / den)
+        print(f"train terms batch {batch} rows {rows}: {err:.2e}, two terms {two:.2e}", flush=True)
+        assert err <= 6e-7
+        assert two > 1.2e-6
