@@ -577,18 +577,20 @@ def decode_bench(args):
     print(json.dumps(result))
 
 
-def train_flops(shape, B, S):
-    """FLOPs the training step executes (2 per multiply-add): the forward, the
-    forward again during the backward (without the down projection), the
-    data-gradient products and the attention backward (seven S x S x d
-    products per head against the forward's two)."""
+def train_flops(shape, B, S, kept):
+    """FLOPs the training step executes (2 per multiply-add), as (weight
+    products, attention): the forward, the forward again during the backward
+    (without the down projection) unless every layer's intermediates are
+    `kept`, the data-gradient products and the attention backward (seven S x S x d
+    products per head against the forward's two).  A product counts once,
+    however many terms it is formed from."""
     D, A, KV, d, F, L = (shape.d_model, shape.n_heads, shape.n_kv_heads, shape.head_dim,
                          shape.d_ffn, shape.n_layers)
     M = B * S
     gemm = 2 * M * (D * (A + 2 * KV) * d + A * d * D + 3 * D * F)
     attn = 2 * A * d * S * (S + 1) * B
-    per_layer = 3 * gemm - 2 * M * D * F + 2 * attn + 3.5 * attn
-    return int(L * per_layer)
+    products = 2 * gemm if kept else 3 * gemm - 2 * M * D * F
+    return L * products, int(L * ((1 if kept else 2) * attn + 3.5 * attn))
 
 
 def train_line(w, seed, dev, steps=2, warmup=1):
@@ -629,16 +631,27 @@ def train_line(w, seed, dev, steps=2, warmup=1):
     e1.record(stream)
     torch.cuda.synchronize()
     ms = e0.elapsed_time(e1) / steps
-    fl = train_flops(shape, B, S)
+    kept = ws.numel() > svl.svl_train_workspace_bytes(cfg, prm, B, N, T)
+    products, attention = train_flops(shape, B, S, kept)
+    fl = products + attention
     tf = fl / (ms * 1e-3) / 1e12
+    if shape.dtype == "bf16":
+        # float32 activations as three bf16 terms on the bf16 matrix pipes
+        terms = 3 * products / (ms * 1e-3) / 1e12
+        rate = {"product_terms": 3, "bf16_term_tflops": round(terms, 1),
+                "bf16_peak_tflops": BF16_PEAK_TFLOPS,
+                "frac_bf16_peak": round(terms / BF16_PEAK_TFLOPS, 4)}
+    else:
+        rate = {"product_terms": 1, "fp32_peak_tflops": FP32_PEAK_TFLOPS,
+                "frac_fp32_peak": round(tf / FP32_PEAK_TFLOPS, 4)}
     print(f"# training step: {ms:.2f} ms", file=sys.stderr, flush=True)
     return {"what": "svl_train_step: static-shape forward under straight-through masks + "
-                    "backward to the token and gate logits, float32",
+                    "backward to the token and gate logits, float32 activations and sums",
             "workload": w.name, "batch": B, "seq_len": S, "prefix": P, "units": U,
             "steps": steps, "warmup": warmup, "ms_per_step": round(ms, 3),
             "tokens_per_s": round(B * S / (ms * 1e-3), 1),
-            "executed_flops_per_step": fl, "executed_tflops": round(tf, 2),
-            "fp32_peak_tflops": FP32_PEAK_TFLOPS, "frac_fp32_peak": round(tf / FP32_PEAK_TFLOPS, 4)}
+            "layers_kept": kept, "executed_flops_per_step": fl,
+            "attention_flops_per_step": attention, "executed_tflops": round(tf, 2), **rate}
 
 
 COMPUTE_BOUND = "llava7b_b8_ragged"
