@@ -100,6 +100,10 @@ __global__ void train_embed_kernel(const T* vision, const T* text, const float* 
   *reinterpret_cast<float4*>(X + m * D + c) = v;
 }
 
+// Rows that a product with bf16 weights reads as they are (normed rows, the
+// gradients of X, of the gate and up values and of Q, K and V) are stored with
+// + 0.0f: they hold no -0 (train_gemm3.hip, split3).
+
 // ------------------------------------------------------------------ RMSNorm
 template <class T>
 __global__ __launch_bounds__(TNT) void train_norm_kernel(const float* X, const T* gain, float eps,
@@ -119,7 +123,8 @@ __global__ __launch_bounds__(TNT) void train_norm_kernel(const float* X, const T
     const float4 v = *reinterpret_cast<const float4*>(x + c);
     const float4 g = ld4(gain, c);
     *reinterpret_cast<float4*>(U + m * D + c) =
-        make_float4(v.x * rr * g.x, v.y * rr * g.y, v.z * rr * g.z, v.w * rr * g.w);
+        make_float4(v.x * rr * g.x + 0.0f, v.y * rr * g.y + 0.0f, v.z * rr * g.z + 0.0f,
+                    v.w * rr * g.w + 0.0f);
   }
 }
 
@@ -149,8 +154,10 @@ __global__ __launch_bounds__(TNT) void train_norm_bwd_kernel(const float* X, con
     const float4 g = ld4(gain, c);
     const float4 d0 = *reinterpret_cast<const float4*>(dRes + m * D + c);
     *reinterpret_cast<float4*>(dX + m * D + c) =
-        make_float4(d0.x + rr * g.x * e.x - v.x * coef, d0.y + rr * g.y * e.y - v.y * coef,
-                    d0.z + rr * g.z * e.z - v.z * coef, d0.w + rr * g.w * e.w - v.w * coef);
+        make_float4((d0.x + rr * g.x * e.x - v.x * coef) + 0.0f,
+                    (d0.y + rr * g.y * e.y - v.y * coef) + 0.0f,
+                    (d0.z + rr * g.z * e.z - v.z * coef) + 0.0f,
+                    (d0.w + rr * g.w * e.w - v.w * coef) + 0.0f);
   }
 }
 
@@ -422,8 +429,8 @@ __global__ void train_rope_kernel(float* X, int64_t ld, int32_t nheads, int32_t 
   const float s = sgn * cs.y;
   float* p = X + m * ld + (int64_t)h * d;
   const float a1 = p[r], a2 = p[r + half];
-  p[r] = a1 * cs.x - a2 * s;
-  p[r + half] = a2 * cs.x + a1 * s;
+  p[r] = (a1 * cs.x - a2 * s) + 0.0f;
+  p[r + half] = (a2 * cs.x + a1 * s) + 0.0f;
 }
 
 // ------------------------------------------------------------------ attention
@@ -852,7 +859,7 @@ __global__ __launch_bounds__(TNT) void train_attn_dkv_kernel(TAttnArgs a) {
     for (int n = 0; n < NBO; ++n) {
       const int64_t off = (base + ki) * ldk + (int64_t)g * HD + 16 * n + lr;
       a.dK[off] = gk[n][r];
-      a.dV[off] = gv[n][r];
+      a.dV[off] = gv[n][r] + 0.0f;
     }
   }
 }
@@ -887,8 +894,8 @@ __global__ __launch_bounds__(TNT) void train_swiglu_bwd_kernel(const float* dHm,
       dot += dh * (x / ex * e);   // H as the forward forms it
       const float sg = 1.0f / ex;
       const float dm = dh * s;
-      AG[q] = dm * e * sg * (1.0f + x * (1.0f - sg));
-      AE[q] = dm * x * sg;
+      AG[q] = dm * e * sg * (1.0f + x * (1.0f - sg)) + 0.0f;
+      AE[q] = dm * x * sg + 0.0f;
     }
     dot = block_sum(dot, red);
     if (threadIdx.x == 0) part[m * U + u] = dot;

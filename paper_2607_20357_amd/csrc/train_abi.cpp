@@ -232,9 +232,10 @@ struct TrainRun {
   // The products of `ops` that share a launch: their own outputs from one A
   // (ksegs = false), or one output, the sum of the products (ksegs = true);
   // R is added to the (one) output; `sl` holds no operand or output of the
-  // launch and nothing that a later one reads.
+  // launch and nothing that a later one reads; neg0: A is the caller's.
   hipError_t products(std::initializer_list<Op> ops, bool ksegs, int32_t bl, Slices sl,
-                      const float* R = nullptr, const float* ascale = nullptr, int32_t kg = 1) const {
+                      const float* R = nullptr, const float* ascale = nullptr, int32_t kg = 1,
+                      bool neg0 = false) const {
     hipError_t e = hipSuccess;
     if (!bf16) {
       const Op* first = ops.begin();
@@ -248,6 +249,7 @@ struct TrainRun {
     TGemm3Args g{};
     g.M = M;
     g.ksegs = ksegs;
+    g.neg0 = neg0;
     for (const Op& o : ops) {
       TSeg& t = g.seg[g.nseg++];
       t.A = o.A;
@@ -330,7 +332,8 @@ struct TrainRun {
     const float2* tab = reinterpret_cast<const float2*>(ws + Lw.rope);
     hipError_t e;
     // FFN branch: dHm = dX2 Wd, then SwiGLU (gate / up gradients replace AG / AE)
-    if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1, {Lw.dO, Lw.end})) != hipSuccess) return e;
+    if ((e = products({{dX2, D, w.w_down, F, f(Lw.dh), F, D}}, false, 1, {Lw.dO, Lw.end}, nullptr,
+                      nullptr, 1, l + 1 == c.n_layers)) != hipSuccess) return e;
     if ((e = launch_train_swiglu_bwd(f(Lw.dh), fl(Lw.ag, l), fl(Lw.ae, l), ms, mstride,
                                      (int32_t)S, M, (int32_t)F, U, f(Lw.pf), st)) != hipSuccess) return e;
     if ((e = products({{fl(Lw.ag, l), F, w.w_gate, D, f(Lw.du), D, F},

@@ -23,33 +23,39 @@ constexpr int G3_NT = 512;                       // 8 waves, 2 x 4 of 64 x 64 ou
 constexpr int G3_PLANE = G3_BM * G3_BK;          // bf16 values of one A term in a stage
 constexpr int G3_STAGE = 3 * G3_PLANE + G3_BN * G3_BK;
 
-// Eight float32 values as three bf16 vectors (truncated to 8 bits each, so
-// hi + mid + lo == x exactly).  An infinity keeps lo = mid = 0 (x == hi); a NaN
-// gives a NaN in mid whatever its payload.
+// Eight float32 values as three bf16 vectors: each term is what is left cut to 8
+// bits one unit below it, so hi + mid + lo == x exactly for |x| >= 2^-109 (below,
+// lo loses less than 2^-133), and none of the three is zero unless x is: times
+// an infinite weight each is an infinity of the same sign, where a zero term would
+// make a NaN.  An infinity has an infinite lo, a NaN is one in every term.
+// x is no -0 (the saturating step would make a NaN of it) unless NEG0, which turns
+// it into +0 first: free where a scale precedes it, 2% of a step elsewhere (8
+// layers, 640 rows: 17.8 ms, 18.15 with it), so the step's kernels store their
+// rows with + 0.0f instead.
+template <bool NEG0>
 __device__ __forceinline__ void split3(const float4& a, const float4& b, uint4& hi, uint4& mid,
                                        uint4& lo) {
   const float x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-  uint32_t m[8], l[8];
+  uint32_t h[8], m[8], l[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) {
-    const float h = __uint_as_float(__float_as_uint(x[i]) & 0xffff0000u);
-    float r = x[i] - h;
-    r = x[i] == h ? 0.0f : r;
-    const float mm = __uint_as_float(__float_as_uint(r) & 0xffff0000u);
-    m[i] = __float_as_uint(r);
-    l[i] = __float_as_uint(r - mm);
+    const float v = NEG0 ? x[i] + 0.0f : x[i];
+    h[i] = __builtin_elementwise_sub_sat(__float_as_uint(v), 1u);
+    const float r = v - __uint_as_float(h[i] & 0xffff0000u);
+    m[i] = __builtin_elementwise_sub_sat(__float_as_uint(r), 1u);
+    l[i] = __float_as_uint(r - __uint_as_float(m[i] & 0xffff0000u));
   }
   // the upper halves of a pair of words, first value in the low half
   auto up = [](uint32_t v0, uint32_t v1) { return __builtin_amdgcn_perm(v1, v0, 0x07060302u); };
-  const uint32_t* u = reinterpret_cast<const uint32_t*>(x);
-  hi = make_uint4(up(u[0], u[1]), up(u[2], u[3]), up(u[4], u[5]), up(u[6], u[7]));
+  hi = make_uint4(up(h[0], h[1]), up(h[2], h[3]), up(h[4], h[5]), up(h[6], h[7]));
   mid = make_uint4(up(m[0], m[1]), up(m[2], m[3]), up(m[4], m[5]), up(m[6], m[7]));
   lo = make_uint4(up(l[0], l[1]), up(l[2], l[3]), up(l[4], l[5]), up(l[6], l[7]));
 }
 
 __device__ __forceinline__ float4 as_f4(const uint4& v) { return __builtin_bit_cast(float4, v); }
 
-// C = R + (s . A) op(B): BL = 0 reads B as [N][K], BL = 1 as [K][N].
+// C = R + (s . A) op(B): BL = 0 reads B as [N][K], BL = 1 as [K][N].  NEG0: A may
+// hold -0 (rows that no kernel of the step wrote).
 //
 // Tile: 128 rows x 256 columns over 8 waves of 64 x 64 (4 x 4 blocks of
 // v_mfma_f32_16x16x32_bf16), K in steps of 32.  Per step the workgroup holds
@@ -72,7 +78,7 @@ __device__ __forceinline__ float4 as_f4(const uint4& v) { return __builtin_bit_c
 // float64, mean of eight seeds, to 0.9e-6 (hidden), 1.4e-6 (token gradients)
 // and 2.2e-6 (gate gradients); float32 MFMA 3.2e-6, 3.7e-6 and 8.1e-6, one level
 // 2.3e-6, 3.6e-6 and 6.0e-6.
-template <int BL, bool ASC>
+template <int BL, bool ASC, bool NEG0>
 __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
   __shared__ __attribute__((aligned(16))) uint16_t sm[2 * G3_STAGE];
   const int tix = xcd_tile_index();
@@ -156,7 +162,7 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
       x1 = make_float4(x1.x * sc[1], x1.y * sc[1], x1.z * sc[1], x1.w * sc[1]);
     }
     uint4 t[3];
-    split3(x0, x1, t[0], t[1], t[2]);
+    split3<ASC || NEG0>(x0, x1, t[0], t[1], t[2]);
 #pragma unroll
     for (int p = 0; p < 3; ++p) *reinterpret_cast<uint4*>(&S[p * G3_PLANE + tid * 8]) = t[p];
     uint16_t* SB = S + 3 * G3_PLANE;
@@ -256,106 +262,6 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
         C[(m0 + row) * ldc + col] = o;
       }
   }
-  bool nan = false;
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      nan |= __builtin_isunordered(total[i][j][0], total[i][j][1]) |
-             __builtin_isunordered(total[i][j][2], total[i][j][3]);
-  if (__builtin_expect(!__any(nan), 1)) return;
-
-  // NaNs: an infinite weight times a middle or low term of zero is one, where
-  // the float32 product is infinite.  If the wave's weights hold a value that is
-  // not finite, those outputs are formed again as float32 products
-  // (v_mfma_f32_16x16x4_f32, operands straight from memory; lane group q takes
-  // k = 8 q + [0, 8) of every 32, in the same order for both operands).  A step
-  // of two layers, 7B shape, 640 rows, takes 4.5 ms, one whose every value is NaN
-  // 11.9 (15.7 as float32 products).
-  const int col = n0 + 64 * wn + (lane & 15);
-  auto segment = [&](int c, int& k) -> const TSeg& {   // of K step c; k: the lane's first
-    int s = sn;
-    if (a.ksegs) {
-      s = 0;
-      while (s + 1 < a.nseg && c >= a.seg[s].chunks) c -= a.seg[s++].chunks;
-    }
-    k = c * G3_BK + 8 * (lane >> 4);
-    return a.seg[s];
-  };
-  auto weights = [&](const TSeg& g, int k, int j, uint32_t (&w)[8]) __attribute__((always_inline)) {
-    const bool in = k < g.K && col + 16 * j < N;
-    const uint16_t* p = static_cast<const uint16_t*>(g.B) +
-                        (in ? (BL == 0 ? (col + 16 * j) * g.ldb + k : k * g.ldb + col + 16 * j) : 0);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) w[e] = in ? (uint32_t)p[BL == 0 ? e : e * g.ldb] << 16 : 0u;
-  };
-  bool special = false;
-#pragma unroll 2
-  for (int c = c_lo; c < c_hi; ++c) {
-    int k;
-    const TSeg& g = segment(c, k);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      uint32_t w[8];
-      weights(g, k, j, w);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) special |= (w[e] & 0x7f800000u) == 0x7f800000u;
-    }
-  }
-  if (!__any(special)) return;
-  uint64_t nans = 0;                             // bit 16 j + 4 i + r: total[i][j][r] is a NaN
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        if (total[i][j][r] != total[i][j][r] && col + 16 * j < N &&
-            64 * wm + 16 * i + 4 * (lane >> 4) + r < rows)
-          nans |= uint64_t(1) << (16 * j + 4 * i + r);
-  for (int i = 0; i < 4; ++i) {
-    // bit 4 j + r: the lane's NaNs in the four blocks of row block i
-    uint32_t bits = 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bits |= ((uint32_t)(nans >> (16 * j + 4 * i)) & 15u) << (4 * j);
-    if (!__any(bits != 0)) continue;
-    const int arow2 = 64 * wm + 16 * i + (lane & 15);
-    const float* scale = ASC && arow2 < rows ? a.ascale + (m0 + arow2) / a.S * a.astride : nullptr;
-    floatx4 sum[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) sum[j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    for (int c = c_lo; c < c_hi; ++c) {
-      int k;
-      const TSeg& g = segment(c, k);
-      float x[8] = {};
-      uint32_t w[4][8];
-      if (k < g.K && arow2 < rows) {
-        const float* p = g.A + (m0 + arow2) * g.lda + k;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          x[e] = p[e];
-          if constexpr (ASC) x[e] *= scale[(uint32_t)(k + e) / (uint32_t)a.kg];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) weights(g, k, j, w[j]);
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-          sum[j] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[e], __uint_as_float(w[j][e]), sum[j], 0, 0, 0);
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        if (!(bits >> (4 * j + r) & 1)) continue;
-        const int64_t row = m0 + 64 * wm + 16 * i + 4 * (lane >> 4) + r;
-        float o = sum[j][r];
-        if (R) o += R[row * a.ldr + col + 16 * j];
-        C[row * ldc + col + 16 * j] = o;
-      }
-  }
 }
 
 // C = R + the K pieces' slices added in piece order, four columns per thread.
@@ -433,11 +339,13 @@ hipError_t launch_train_gemm3(const TGemm3Args& a, int32_t bl, hipStream_t st) {
   if (a.ksplit > 1 && !a.part) return hipErrorInvalidValue;
   const unsigned grid = (unsigned)((a.ntiles + 7) / 8 * 8);
   if (bl == 0) {
-    if (a.ascale) train_gemm3_kernel<0, true><<<grid, G3_NT, 0, st>>>(a);
-    else train_gemm3_kernel<0, false><<<grid, G3_NT, 0, st>>>(a);
+    if (a.ascale) train_gemm3_kernel<0, true, false><<<grid, G3_NT, 0, st>>>(a);
+    else if (a.neg0) return hipErrorInvalidValue;
+    else train_gemm3_kernel<0, false, false><<<grid, G3_NT, 0, st>>>(a);
   } else {
     if (a.ascale) return hipErrorInvalidValue;
-    train_gemm3_kernel<1, false><<<grid, G3_NT, 0, st>>>(a);
+    if (a.neg0) train_gemm3_kernel<1, false, true><<<grid, G3_NT, 0, st>>>(a);
+    else train_gemm3_kernel<1, false, false><<<grid, G3_NT, 0, st>>>(a);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.ksplit <= 1) return e;

@@ -73,6 +73,7 @@ struct TGemm3Args {
   TSeg seg[3];
   int32_t nseg;
   bool ksegs;
+  bool neg0;            // A may hold -0 (bl == 1); otherwise, without ascale, it holds none
   int64_t M;
   const float* R;       // nullptr, or added to C (one output, another array)
   int64_t ldr;

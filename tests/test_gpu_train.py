@@ -372,3 +372,47 @@ def test_train_bf16_products_keep_all_three_terms(batch, rows):
         print(f"train terms batch {batch} rows {rows}: {err:.2e}, two terms {two:.2e}", flush=True)
         assert err <= 6e-7
         assert two > 1.2e-6
+
+
+def test_train_bf16_negative_zeros():
+    """-0 among the factors of bf16-weight products, whose three-term split has no
+    place for it: zeroed tokens under gains of both signs, unit masks of 0 times
+    negative values, text rows of -0 and a gradient with entries of -0.  Same
+    bits as with +0 in the caller's tensors, and the float64 forward's values."""
+    base = _tiny(2)
+    shape = dataclasses.replace(base.shape, n_layers=2, d_model=320, n_heads=4, n_kv_heads=2, head_dim=64,
+                                d_ffn=768, n_groups=4, dtype="bf16")
+    N, T = 60, 30
+    w = dataclasses.replace(base, shape=shape, n_vision=N, n_text=T, name="train_neg_zero")
+    cfg = svl.make_config(shape)
+    vision, text = W.draw_hidden(w, 18, device="cuda")
+    layers = [dict(W.draw_layer_weights(w, l, 18, device="cuda")) for l in range(2)]
+    for l in layers:
+        for name in ("attn_norm", "ffn_norm"):
+            l[name] = l[name].clone()
+            l[name][::2] *= -1
+    rng = np.random.default_rng(18)
+    t = lambda *sh: torch.from_numpy(rng.standard_normal(sh).astype(np.float32)).cuda()
+    z, G = t(2, N), t(2, N + T, 320)
+    g = torch.tensor([[1.0, -1.0, 1.0, -1.0], [-1.0, 1.0, -1.0, -1.0]], device="cuda")
+    G[:, ::3] = 0.0
+    text[:, 5:9] = 0.0
+    prm = svl.svl_train_params(0.7, 1.3, 1, 4)
+    ws = svl.alloc_train_workspace(cfg, prm, 2, N, T)
+    table = svl.LayerTable(layers)
+    outs = []
+    for zero in (0.0, -0.0):
+        G[:, ::3] = zero
+        text[:, 5:9] = zero
+        ws.fill_(255)
+        outs.append(svl.svl_train_step(cfg, table, prm, z, g, vision, text, G, ws))
+    torch.cuda.synchronize()
+    for k, v in outs[0].items():
+        assert torch.equal(v, outs[1][k]), k
+        assert torch.isfinite(v.float()).all(), k
+    hl = [{k: v.double().cpu() for k, v in l.items()} for l in layers]
+    for b in range(2):
+        x = torch.cat([vision[b].double() * (z[b] > 0).double()[:, None], text[b].double()]).cpu()
+        ref = _forward64(shape, hl, x, (g[b].cpu() > 0).double().reshape(1, 4), 1, 4)
+        err = float((outs[1]["hidden"][b].double().cpu() - ref).abs().max() / ref.abs().max())
+        assert err <= 1e-6, err
