@@ -39,19 +39,6 @@ constexpr int KS = 4;                          // K chunks per weight stage (one
 constexpr int LDS_STRIDE = KS * MFMA_BK;       // 16-bit elements per LDS row (512 B, 32 units)
 constexpr int MAX_CHUNKS = 1024;               // K chunks per tile (K <= 65536)
 
-// LDS row swizzle.  gfx950's LDS serves a 16-byte-per-lane access half a
-// wave at a time, 512 bytes over 128 four-byte banks, so the 32 lanes must
-// hit 32 distinct 16-byte units modulo 32.  A weight row of a stage is 32
-// units (4 chunks x 8); unit v of tile row r is stored at v ^ swz(r).  The
-// fragment reads (16 rows x lane groups 0, 1 or 2, 3) and the stores (one
-// row's 32 units per half wave) are then conflict-free.
-__device__ __forceinline__ int swz(int r) { return (r & 1) | (((r >> 1) & 7) << 2); }
-
-// Weights are streamed once: non-temporal loads.
-__device__ __forceinline__ uint4 load16w(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 2));
-}
-
 template <int P>
 using Phase = std::integral_constant<int, P>;
 
