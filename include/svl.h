@@ -399,9 +399,12 @@ svl_status svl_workspace_status(const void *ws, size_t ws_bytes, uint32_t *statu
  * with y = sigma((logit + xi) / tau).  The budget term's gradient
  * (svl_budget_loss) is separate; the total gradient is the sum.
  *
- * Arithmetic: float32 throughout (weights and embeddings widened exactly
- * from the storage dtype; svl_config.compute is ignored); the forward of each
- * layer is recomputed from its stored input during the backward unless the
+ * Arithmetic: float32 activations, gradients and sums (svl_config.compute is
+ * ignored).  Embeddings are widened exactly from the storage dtype.  Products
+ * with bf16 weights take each float32 factor as three bf16 terms, whose sum is
+ * the factor (exact for magnitudes of 2^-109 and more), and add their exact
+ * products in float32; float32 weights are multiplied as they are.  The forward
+ * of each layer is recomputed from its stored input during the backward unless the
  * workspace holds every layer's intermediates.
  * Requirements beyond the config's: head_dim in {32, 64, 128}; d_model and
  * d_ffn multiples of 16; n_heads and d_ffn divisible by units, d_ffn / units

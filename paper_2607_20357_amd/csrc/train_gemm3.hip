@@ -1,10 +1,11 @@
 // Products of the training path with bf16 weights: float32 activations times
 // bf16 weights, float32 accumulation, on the bf16 matrix pipes.
 //
-// A float32 value is the exact sum of three bf16 values (its significand cut
-// into 8 + 8 + 8 bits), and a product of two bf16 values is exact in float32,
-// so  x w = hi w + mid w + lo w  costs three bf16 MFMAs and rounds only in
-// the float32 accumulator, as the float32 MFMA does.  bf16 MFMA runs at 16
+// A float32 value of magnitude 2^-109 or more is the exact sum of three bf16
+// values (split3), and a product of two bf16 values is exact in float32 short of
+// underflow, so  x w = hi w + mid w + lo w  costs three bf16 MFMAs and rounds
+// only in the float32 accumulator, as the float32 MFMA does.  Below 2^-109 the
+// terms miss less than 2^-133 of x.  bf16 MFMA runs at 16
 // times the float32 rate, so three terms are worth it (per-launch figures at
 // train_gemm3_kernel).
 #include <hip/hip_runtime.h>
@@ -60,8 +61,9 @@ __device__ __forceinline__ float4 as_f4(const uint4& v) { return __builtin_bit_c
 // Tile: 128 rows x 256 columns over 8 waves of 64 x 64 (4 x 4 blocks of
 // v_mfma_f32_16x16x32_bf16), K in steps of 32.  Per step the workgroup holds
 // the three terms of A (24 KB) and B (16 KB) in LDS, in fragment order (a
-// 16 x 32 block is 1 KB, lane l's 16 bytes at 16 l), so every LDS access is
-// conflict-free; two such stages, one barrier each.  Next step's operands
+// 16 x 32 block is 1 KB, lane l's 16 bytes at 16 l), free of bank conflicts (BL = 1,
+// whose columns are transposed on the way in: 0.8 conflict cycles an LDS
+// instruction); two such stages, one barrier each.  Next step's operands
 // wait in registers: the split costs about 8 VALU operations per value, once per
 // workgroup, and is done by waves 0-3 before their products and by waves 4-7
 // after theirs, so the two waves of a SIMD alternate between the vector and
@@ -69,15 +71,16 @@ __device__ __forceinline__ float4 as_f4(const uint4& v) { return __builtin_bit_c
 //
 // Three terms make the tile compute-bound: a step is 1536 cycles of MFMA per
 // SIMD against 32 KB of loads and 168 KB of LDS traffic.  At 640 rows, 7B shape
-// (float32 MFMA with 64 x 64 tiles before): Q, K and V in one launch 183 us
-// (three launches of 200 us), gate and up 309 (1000), output 69 + 11 for the
-// slices (224), down 167 + 11 (600), the gradients of gate and up in one launch
-// 318 + 8 (1100): 0.96-1.12 PFLOP/s of bf16 products, where a library product
-// of 8192^3 reaches 1.15 on the same card.  Sums in two
+// (float32 MFMA with 64 x 64 tiles before): Q, K and V in one launch 181 us
+// (three launches of 200 us), gate and up 353 (1000), output 71 + 10 for the
+// slices (224), down 164 + 11 (600), the gradients of gate and up in one launch
+// 321 + 8 (1100): 0.91-1.08 PFLOP/s of bf16 products without the slices, 0.80-1.07
+// with them, where a library product of 8192^3 reaches 1.15 on the same card;
+// the matrix pipes are 47-49% busy.  Sums in two
 // levels (below) cost 4% of that and bring the error of a two-layer step against
-// float64, mean of eight seeds, to 0.9e-6 (hidden), 1.4e-6 (token gradients)
-// and 2.2e-6 (gate gradients); float32 MFMA 3.2e-6, 3.7e-6 and 8.1e-6, one level
-// 2.3e-6, 3.6e-6 and 6.0e-6.
+// float64 to 0.9e-6 (hidden), 1.5e-6 (token gradients) and 1.3e-6 (gate gradients),
+// medians of 700 seeds; float32 MFMA 3.2e-6, 3.7e-6 and 8.1e-6, one level 2.3e-6,
+// 3.6e-6 and 6.0e-6, means of eight.
 template <int BL, bool ASC, bool NEG0>
 __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
   __shared__ __attribute__((aligned(16))) uint16_t sm[2 * G3_STAGE];
