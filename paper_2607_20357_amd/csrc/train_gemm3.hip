@@ -245,11 +245,11 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
   }
 
   // total[i][j][r] = C[64 wm + 16 i + 4 (lane / 16) + r][64 wn + 16 j + lane % 16]
-  const bool split = a.ksplit > 1;
-  float* C = split ? a.part + (int64_t)piece * a.M * a.ncols + (a.ksegs ? 0 : a.seg[sn].col0)
+  // (piece 0 of a split in its place in C, the others in their slices)
+  float* C = piece ? a.part + (int64_t)(piece - 1) * a.M * a.ncols + (a.ksegs ? 0 : a.seg[sn].col0)
                    : a.seg[sn].C;
-  const int64_t ldc = split ? a.ncols : a.seg[sn].ldc;
-  const float* R = split ? nullptr : a.R;
+  const int64_t ldc = piece ? a.ncols : a.seg[sn].ldc;
+  const float* R = a.ksplit > 1 ? nullptr : a.R;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     const int col = n0 + 64 * wn + 16 * j + (lane & 15);
@@ -267,27 +267,28 @@ __global__ __launch_bounds__(G3_NT, 1) void train_gemm3_kernel(TGemm3Args a) {
   }
 }
 
-// C = R + the K pieces' slices added in piece order, four columns per thread.
+// C = R + the K pieces added in order (the first is in C), four columns per thread.
 __global__ void train_reduce3_kernel(TGemm3Args a) {
   const int n4 = a.ncols / 4;
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q >= a.M * n4) return;
   const int64_t m = q / n4;
   const int c = (int)(q % n4) * 4;
-  float4 s = *reinterpret_cast<const float4*>(a.part + m * a.ncols + c);
-  for (int z = 1; z < a.ksplit; ++z) {
-    const float4 p = *reinterpret_cast<const float4*>(a.part + (z * a.M + m) * a.ncols + c);
-    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
-  }
   int sn = 0;
   if (!a.ksegs)
     while (sn + 1 < a.nseg && c >= a.seg[sn + 1].col0) ++sn;
   const int cc = a.ksegs ? c : c - a.seg[sn].col0;
+  float4* out = reinterpret_cast<float4*>(a.seg[sn].C + m * a.seg[sn].ldc + cc);
+  float4 s = *out;
+  for (int z = 1; z < a.ksplit; ++z) {
+    const float4 p = *reinterpret_cast<const float4*>(a.part + ((z - 1) * a.M + m) * a.ncols + c);
+    s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+  }
   if (a.R) {
     const float4 r = *reinterpret_cast<const float4*>(a.R + m * a.ldr + cc);
     s.x = r.x + s.x; s.y = r.y + s.y; s.z = r.z + s.z; s.w = r.w + s.w;
   }
-  *reinterpret_cast<float4*>(a.seg[sn].C + m * a.seg[sn].ldc + cc) = s;
+  *out = s;
 }
 
 }  // namespace
@@ -301,7 +302,7 @@ KPieces train_gemm3_pieces(int64_t M, int64_t mtiles_x_ntiles, int64_t ncols, in
   double best_t = -1.0;
   for (int64_t ns = 1; ns <= 8; ++ns) {
     const int64_t cp = (nchunks + ns - 1) / ns;
-    if (ns > 1 && (cp < 8 || cp * (ns - 1) >= nchunks || ns * M * ncols > slice_floats)) break;
+    if (ns > 1 && (cp < 8 || cp * (ns - 1) >= nchunks || (ns - 1) * M * ncols > slice_floats)) break;
     const double rounds = (double)((mtiles_x_ntiles * ns + 255) / 256);
     // a step takes about 0.9 us; slices are written and read at about 4 TB/s
     double t = rounds * (double)(cp + 5) * 0.9;

@@ -80,7 +80,7 @@ struct TGemm3Args {
   const float* ascale;  // as in TGemmArgs (nseg == 1)
   int64_t astride;
   int32_t S, kg;
-  float* part;          // slices [ksplit][M][ncols] when ksplit > 1
+  float* part;          // slices [ksplit - 1][M][ncols] of the pieces after the first
   // filled by train_gemm3_plan: tiles, output columns, K steps of 32 and pieces
   int32_t mtiles, ntn, ncols, nchunks, ksplit, cpiece, ntiles;
 };
@@ -88,7 +88,7 @@ struct KPieces {
   int32_t ns;
   int64_t chunks;
 };
-// Pieces whose slices fit `slice_floats`.
+// Pieces whose slices (one each after the first) fit `slice_floats`.
 void train_gemm3_plan(TGemm3Args& a, int64_t slice_floats);
 hipError_t launch_train_gemm3(const TGemm3Args& a, int32_t bl, hipStream_t st);
 
